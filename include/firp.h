@@ -58,7 +58,7 @@ typedef struct {
   int32_t max_ctx;   /* committed tokens the cache can hold, per sequence */
   int32_t max_batch; /* independent sequences */
   int32_t max_nodes; /* N, tree nodes including the root */
-  int32_t max_rows;  /* N + k*|A| <= FIRP_MAX_ROWS; also the prefill chunk length */
+  int32_t max_rows;  /* N + k*|A| <= FIRP_MAX_ROWS */
   int32_t b_max;     /* top-b kept per pseudo row, 1..FIRP_MAX_B */
 } firp_model_desc;
 

@@ -192,27 +192,35 @@ void launch_rope_kv_tiles(const Partial& qkv, const RowScale& rs, int n_q_heads,
   }
 }
 
-template <int DH>
+// CHAIN: the rows are a prompt chunk of one sequence, row i follows row i - 1 (its mask is "i and
+// everything before", so none is read), and there may be hundreds of them: a workgroup takes one
+// block of NWAVES * PAIRS pairs (blockIdx.z) and only the keys up to the block's last row.  The
+// blocks with most keys are dealt first.
+template <int DH, bool CHAIN>
 __global__ __launch_bounds__(64 * NWAVES, 1) void k_attention_mfma(const bf16* __restrict__ q_frag,
                                                           int n_q_heads, SeqRows sr, int n_local,
                                                           const unsigned long long* __restrict__ row_mask,
                                                           const int* __restrict__ p0v, int seq0, KvView kv,
                                                           float* __restrict__ part_o, float* __restrict__ part_ml,
-                                                          int splits) {
+                                                          int splits, Act out) {
   constexpr int DS = DH / 32;       // k-steps of the score product
   constexpr int DT = DH / 16;       // 16-dim tiles of the output
   constexpr int NF = 2 * DS + DT;   // operand fragments (64 lanes x 16 B) of one 32-key block
   constexpr int FPW = (NF + NWAVES - 1) / NWAVES;   // fragments each wave fetches
   static_assert(NF % NWAVES == 0 || NF < NWAVES, "fragments must divide over the waves");
-  const int split = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
+  const int split = blockIdx.x, hk = blockIdx.y, b = CHAIN ? 0 : blockIdx.z;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r16 = lane & 15, kb = lane >> 4;
   const int G = n_q_heads / kv.n_kv_heads;
   const int n_tiles = (n_local + 15) >> 4;
-  const int n_pairs = n_tiles * G;
+  const int pair_lo = CHAIN ? (gridDim.z - 1 - blockIdx.z) * (NWAVES * PAIRS) : 0;
+  const int n_pairs = CHAIN ? min(n_tiles * G, pair_lo + NWAVES * PAIRS) : n_tiles * G;
+  // rows [row_lo, row_hi) of the sequence are this workgroup's
+  const int row_lo = CHAIN ? pair_lo / G * 16 : 0;
+  const int row_hi = CHAIN ? min(n_local, ((n_pairs - 1) / G + 1) * 16) : n_local;
   const int bs = seq0 + b;   // sequence whose cache this launch reads (b counts inside the launch)
   const int p0 = p0v[bs];
-  const int n_keys = p0 + n_local;
+  const int n_keys = p0 + row_hi;
   // The sequence's keys in `splits` chunks of whole 32-key blocks.  The chunk length follows
   // from the committed length on the device, so that no launch argument changes from step to
   // step (a captured launch can be replayed as the context grows).
@@ -220,8 +228,9 @@ __global__ __launch_bounds__(64 * NWAVES, 1) void k_attention_mfma(const bf16* _
   const int key_begin = split * chunk;
   if (key_begin >= n_keys) {
     // a split past the end of a short context: leave the neutral element (weight 0) for the merge
-    for (int idx = threadIdx.x; idx < n_local * G; idx += blockDim.x) {
+    for (int idx = row_lo * G + threadIdx.x; idx < row_hi * G; idx += blockDim.x) {
       const int local = idx / G, head = hk * G + idx % G;
+      if (CHAIN && ((local >> 4) * G + idx % G < pair_lo || (local >> 4) * G + idx % G >= n_pairs)) continue;
       const size_t base = ((size_t)global_row(sr, b, local) * n_q_heads + head) * splits + split;
       part_ml[base * 2 + 0] = -__builtin_inff();
       part_ml[base * 2 + 1] = 0.f;
@@ -241,7 +250,7 @@ __global__ __launch_bounds__(64 * NWAVES, 1) void k_attention_mfma(const bf16* _
   __shared__ u32x4_t kv_lds[2][NF][64];
   // every row's mask words (two zero words behind them) sit in its wave's corner of LDS, where
   // the blocks that reach past the committed cache pick the word they need by index
-  __shared__ unsigned long long mk_lds[NWAVES * PAIRS * 16][FIRP_MASK_WORDS + 2];
+  __shared__ unsigned long long mk_lds[CHAIN ? 1 : NWAVES * PAIRS * 16][FIRP_MASK_WORDS + 2];
 
   // This wave fetches fragments f = NWAVES*j + wave (with fewer fragments than waves, several
   // waves fetch and store the same one).  Fragments [0, 2*DS) are K: (16-key tile t2,
@@ -275,9 +284,9 @@ __global__ __launch_bounds__(64 * NWAVES, 1) void k_attention_mfma(const bf16* _
   };
 
   // a sweep covers up to NWAVES * PAIRS pairs: pair `first + wave + NWAVES*p` is this wave's p-th
-  const int n_sweeps = (n_pairs + NWAVES * PAIRS - 1) / (NWAVES * PAIRS);
+  const int n_sweeps = (n_pairs - pair_lo + NWAVES * PAIRS - 1) / (NWAVES * PAIRS);
   for (int sweep = 0; sweep < n_sweeps; ++sweep) {
-    const int first = sweep * NWAVES * PAIRS;
+    const int first = pair_lo + sweep * NWAVES * PAIRS;
     int n_live = 0;
 #pragma unroll
     for (int p = 0; p < PAIRS; ++p) n_live += first + wave + NWAVES * p < n_pairs;
@@ -285,7 +294,7 @@ __global__ __launch_bounds__(64 * NWAVES, 1) void k_attention_mfma(const bf16* _
     // hits and are asked for first (loads return in order); the first three K/V blocks follow.
     u32x4_t q[PAIRS][DS][2];
     unsigned long long mw[PAIRS][FIRP_MASK_WORDS];
-    int row_of[PAIRS], head_of[PAIRS];
+    int row_of[PAIRS], head_of[PAIRS], local_of[PAIRS];
 #pragma unroll
     for (int p = 0; p < PAIRS; ++p) {
       int pi = min(first + wave + NWAVES * p, n_pairs - 1);
@@ -293,6 +302,7 @@ __global__ __launch_bounds__(64 * NWAVES, 1) void k_attention_mfma(const bf16* _
       int local = min(tile * 16 + r16, n_local - 1);
       int row = global_row(sr, b, local);
       row_of[p] = (tile * 16 + r16 < n_local) ? row : -1;
+      local_of[p] = local;
       head_of[p] = hk * G + g;
       if (p < n_live) {
         const bf16* fb = q_frag + ((size_t)(b * n_tiles + tile) * n_q_heads + head_of[p]) * (size_t)(DS * 2 * 512) + lane * 8;
@@ -305,14 +315,15 @@ __global__ __launch_bounds__(64 * NWAVES, 1) void k_attention_mfma(const bf16* _
 #pragma unroll
         for (int ds = 0; ds < DS; ++ds) q[p][ds][0] = q[p][ds][1] = u32x4_t{0, 0, 0, 0};
       }
+      if constexpr (!CHAIN)
 #pragma unroll
-      for (int wd = 0; wd < FIRP_MASK_WORDS; ++wd) mw[p][wd] = row_mask[(size_t)row * FIRP_MASK_WORDS + wd];
+        for (int wd = 0; wd < FIRP_MASK_WORDS; ++wd) mw[p][wd] = row_mask[(size_t)row * FIRP_MASK_WORDS + wd];
     }
     u32x4_t g0[FPW], g1[FPW], g2[FPW];
     fetch(g0, 0, hard_last);
     fetch(g1, 1, hard_last);
     fetch(g2, 2, hard_last);
-    if (kb == 0) {
+    if (!CHAIN && kb == 0) {
 #pragma unroll
       for (int p = 0; p < PAIRS; ++p) {
         unsigned long long* mrow = mk_lds[(wave * PAIRS + p) * 16 + r16];
@@ -365,9 +376,12 @@ __global__ __launch_bounds__(64 * NWAVES, 1) void k_attention_mfma(const bf16* _
         const int c0 = k0 + 8 * kb - p0;  // step-local index of the lane's first key
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-          const unsigned long long* mrow = mk_lds[(wave * PAIRS + p) * 16 + r16];
+          const unsigned long long* mrow = mk_lds[CHAIN ? 0 : (wave * PAIRS + p) * 16 + r16];
           unsigned vis;
-          if (c0 <= -8) {
+          if constexpr (CHAIN) {
+            const int last_seen = local_of[p] - c0;   // of the lane's eight keys
+            vis = last_seen >= 7 ? 0xffu : last_seen < 0 ? 0u : (2u << last_seen) - 1u;
+          } else if (c0 <= -8) {
             vis = 0xffu;
           } else if (c0 < 0) {
             vis = (unsigned)(mrow[0] << (-c0)) | ((1u << (-c0)) - 1u);
@@ -392,9 +406,11 @@ __global__ __launch_bounds__(64 * NWAVES, 1) void k_attention_mfma(const bf16* _
       // The reference point m_run of the exponentials only has to stay within 2^8 of the true
       // running maximum (any reference gives the same quotient in the end), so the rescale of
       // the accumulators is taken only when some row of a tile moved further than that.
+      // (Rows past the end of the last tile hold whatever the fragment buffer held; they must not
+      // decide it, or equal inputs could round differently.)
       bool moved = false;   // stays false for a row with nothing visible yet
 #pragma unroll
-      for (int p = 0; p < NP; ++p) moved |= mx[p] > m_run[p] + 8.0f;
+      for (int p = 0; p < NP; ++p) moved |= row_of[p] >= 0 && mx[p] > m_run[p] + 8.0f;
       if (__builtin_amdgcn_ballot_w64(moved) != 0ull) {
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
@@ -468,6 +484,14 @@ __global__ __launch_bounds__(64 * NWAVES, 1) void k_attention_mfma(const bf16* _
       float l = l_run[p];
       l += __shfl_xor(l, 16, 64);
       l += __shfl_xor(l, 32, 64);
+      if (splits == 1) {   // nothing to merge: this is the result
+        const float inv = 1.0f / l;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+          act_store4<true>(out, (size_t)row_of[p] * out.ld + (size_t)head_of[p] * DH + dt * 16 + 4 * kb, o[p][dt][0] * inv,
+                           o[p][dt][1] * inv, o[p][dt][2] * inv, o[p][dt][3] * inv);
+        continue;
+      }
       size_t base = ((size_t)row_of[p] * n_q_heads + head_of[p]) * splits + split;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) *(f32x4_t*)(part_o + base * DH + dt * 16 + 4 * kb) = o[p][dt];
@@ -523,31 +547,40 @@ bool attention_mfma_supported(int head_dim, int dtype) {
   return dtype == DT_BF16 && (head_dim == 32 || head_dim == 64 || head_dim == 128);
 }
 
-size_t attention_mfma_scratch_floats(int rows, int n_q_heads, int head_dim) {
-  return (size_t)rows * n_q_heads * FIRP_ATTN_MAX_SPLITS * (head_dim + 2);
+size_t attention_mfma_scratch_floats(int rows, int chunk_rows, int n_q_heads, int head_dim) {
+  const size_t one_block = std::min(chunk_rows, NWAVES * PAIRS * 16);   // a chunk of one block may be split as often as a step
+  return std::max({(size_t)rows * FIRP_ATTN_MAX_SPLITS, one_block * FIRP_ATTN_MAX_SPLITS,
+                   (size_t)chunk_rows * FIRP_ATTN_CHUNK_SPLITS}) * n_q_heads * (head_dim + 2);
 }
 
 void launch_attention_mfma(const bf16* q_frag, int rows, int n_q_heads, int B, int n_real_per_seq, int n_pseudo_per_seq,
-                           int n_anchor_per_seq, int seq0, const RowTab& rt, const int* p0, int max_ctx_now, const KvView& kv, float* scratch,
-                           const Act& out, hipStream_t s) {
+                           int n_anchor_per_seq, int seq0, bool chain, const RowTab& rt, const int* p0, int max_ctx_now,
+                           const KvView& kv, float* scratch, const Act& out, hipStream_t s) {
   const int n_local = n_real_per_seq + n_pseudo_per_seq;
   const int dh = kv.head_dim;
   SeqRows sr{n_real_per_seq, std::max(1, n_anchor_per_seq), B * n_real_per_seq, B * n_anchor_per_seq};
   // about one workgroup per CU; the count of splits depends on the context length only while the
   // context is shorter than that many 32-key blocks
+  const int pairs = (n_local + 15) / 16 * (n_q_heads / kv.n_kv_heads);
+  const int z = chain ? (pairs + NWAVES * PAIRS - 1) / (NWAVES * PAIRS) : B;
   int n_keys = max_ctx_now + n_local;
   int blocks = (n_keys + 31) / 32;
-  int want = std::max(1, 256 / std::max(1, kv.n_kv_heads * B));
-  int splits = std::max(1, std::min({want, blocks, FIRP_ATTN_MAX_SPLITS}));
+  int want = std::max(1, 256 / std::max(1, kv.n_kv_heads * z));
+  int splits = std::max(1, std::min({want, blocks, chain && z > 1 ? FIRP_ATTN_CHUNK_SPLITS : FIRP_ATTN_MAX_SPLITS}));
   float* part_o = scratch;
-  float* part_ml = scratch + (size_t)rows * n_q_heads * FIRP_ATTN_MAX_SPLITS * dh;
-  dim3 g(splits, kv.n_kv_heads, B), blk(64 * NWAVES);
-  if (dh == 128)
-    hipLaunchKernelGGL(k_attention_mfma<128>, g, blk, 0, s, q_frag, n_q_heads, sr, n_local, rt.mask, p0, seq0, kv, part_o, part_ml, splits);
-  else if (dh == 64)
-    hipLaunchKernelGGL(k_attention_mfma<64>, g, blk, 0, s, q_frag, n_q_heads, sr, n_local, rt.mask, p0, seq0, kv, part_o, part_ml, splits);
-  else
-    hipLaunchKernelGGL(k_attention_mfma<32>, g, blk, 0, s, q_frag, n_q_heads, sr, n_local, rt.mask, p0, seq0, kv, part_o, part_ml, splits);
+  float* part_ml = scratch + (size_t)rows * n_q_heads * splits * dh;
+  dim3 g(splits, kv.n_kv_heads, z), blk(64 * NWAVES);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, g, blk, 0, s, q_frag, n_q_heads, sr, n_local, rt.mask, p0, seq0, kv, part_o, part_ml, splits, out);
+  };
+  if (dh == 128) {
+    if (chain) go(k_attention_mfma<128, true>); else go(k_attention_mfma<128, false>);
+  } else if (dh == 64) {
+    if (chain) go(k_attention_mfma<64, true>); else go(k_attention_mfma<64, false>);
+  } else {
+    if (chain) go(k_attention_mfma<32, true>); else go(k_attention_mfma<32, false>);
+  }
+  if (splits == 1) return;
   int hpb = std::max(1, 256 / (dh / 4));
   dim3 gc(rows, (n_q_heads + hpb - 1) / hpb), bc(dh / 4, hpb);
   hipLaunchKernelGGL(k_attn_combine<true>, gc, bc, 0, s, part_o, part_ml, splits, n_q_heads, dh, out);

@@ -16,6 +16,11 @@ using namespace firp;
 // Rows of the partial-sum buffer are padded by one 128-byte line: projection widths are
 // multiples of 1024 floats, and rows a multiple of 4 KB apart would all fall on one memory channel.
 #define FIRP_PART_PAD 32
+// Rows of a prompt chunk of a bf16 model.  A chunk streams every weight once, and the kernels between
+// the projections cost about the same for 128 rows as for 512: with chunks of 128 rows a 1024-token
+// prompt of the 13B shape took 87.6 ms and an 8192-token one of the 7B shape 432 ms, with 1024 rows
+// 66.5 and 313 ms (the projections then run at the matrix units' rate, and more rows gain nothing).
+#define FIRP_CHUNK_ROWS 1024
 
 namespace {
 
@@ -105,6 +110,7 @@ struct firp_ctx {
   bool packed = false;
   // geometry
   int Rmax = 0, Rpad = 0, slots = 0, qkv_ld = 0, esize = 0;
+  int Rwork = 0;   // rows the working buffers hold: a step's (Rpad) or a prompt chunk's, whichever is more
   size_t kv_layer_stride = 0, kv_seq_stride = 0;
   // device buffers
   float* x = nullptr;
@@ -118,6 +124,7 @@ struct firp_ctx {
   unsigned long long* rt_mask = nullptr;
   int *tt_parent = nullptr, *tt_level = nullptr, *tt_rank = nullptr, *tt_cstart = nullptr,
       *tt_clist = nullptr, *tt_pbase = nullptr, *pseudo_src = nullptr, *injected = nullptr;
+  int* prompt_tok = nullptr;   // the prompts of the running prefill
   SeqState st{};
   // host state
   int batch = 0;
@@ -193,22 +200,22 @@ bool desc_ok(const firp_model_desc* d, int k, std::string& why) {
 size_t carve(firp_ctx* c, char* base) {
   const firp_model_desc& d = c->d;
   Carver cv{base};
-  int R = c->Rmax, Rp = c->Rpad;
+  int R = c->Rmax, Rp = c->Rpad, Rw = c->Rwork;
   size_t es = c->esize;
   int qd = d.n_q_heads * d.head_dim;
-  c->x = cv.take<float>((size_t)Rp * d.d_model);
+  c->x = cv.take<float>((size_t)Rw * d.d_model);
   c->part = cv.take<float>(c->part_elems);
   c->logits = cv.take<float>((size_t)Rp * d.vocab);
-  c->attn_scratch = cv.take<float>(attention_mfma_scratch_floats(Rp, d.n_q_heads, d.head_dim));
-  c->rope_tab = cv.take<float2>((size_t)Rp * d.head_dim / 2);
+  c->attn_scratch = cv.take<float>(attention_mfma_scratch_floats(Rp, Rw, d.n_q_heads, d.head_dim));
+  c->rope_tab = cv.take<float2>((size_t)Rw * d.head_dim / 2);
   c->argmax_scratch = cv.take<char>(argmax_scratch_bytes(Rp, d.b_max));
-  c->norm_ss = cv.take<float>((size_t)Rp * FIRP_NORM_PIECES);
-  c->q_frag = cv.take<bf16>(attention_q_frag_elems(Rp, d.max_batch, d.n_q_heads, d.head_dim));
+  c->norm_ss = cv.take<float>((size_t)Rw * FIRP_NORM_PIECES);
+  c->q_frag = cv.take<bf16>(attention_q_frag_elems(Rw, d.max_batch, d.n_q_heads, d.head_dim));
   auto act = [&](Act& a, int ld) {
     a.ld = ld;
     a.f32 = cv.take<float>((size_t)Rp * ld);
-    a.hi = cv.take<bf16>((size_t)Rp * ld);
-    a.lo = cv.take<bf16>((size_t)Rp * ld);
+    a.hi = cv.take<bf16>((size_t)Rw * ld);
+    a.lo = cv.take<bf16>((size_t)Rw * ld);
   };
   act(c->act_d, d.d_model);
   act(c->act_q, qd);
@@ -263,6 +270,7 @@ size_t carve(firp_ctx* c, char* base) {
     for (auto& sl : c->slot) sl.base = cv.take<char>(t.bytes);
   }
   c->injected = cv.take<int>(R);
+  c->prompt_tok = cv.take<int>((size_t)d.max_batch * d.max_ctx);
   int B = d.max_batch;
   c->st.p0 = cv.take<int>(B);
   c->st.root_tok = cv.take<int>(B);
@@ -290,8 +298,16 @@ void setup_geometry(firp_ctx* c, const firp_model_desc* d, int k) {
   c->kv_layer_stride = (size_t)d->n_kv_heads * c->slots * d->head_dim;
   c->kv_seq_stride = (size_t)d->n_layers * c->kv_layer_stride;
   // split-K partial sums: the widest projection output times the largest split factor used
-  size_t widest = std::max<size_t>({(size_t)d->vocab, (size_t)2 * d->d_ffn, (size_t)c->qkv_ld, (size_t)d->d_model});
+  size_t widest_layer = std::max<size_t>({(size_t)2 * d->d_ffn, (size_t)c->qkv_ld, (size_t)d->d_model});
+  size_t widest = std::max<size_t>((size_t)d->vocab, widest_layer);
   c->part_elems = (size_t)c->Rpad * (widest + FIRP_PART_PAD) * 8;
+  // prompt chunks of bf16 models: FIRP_CHUNK_ROWS rows at a time (see firp_prefill), which fill the
+  // chip without splitting K much
+  c->Rwork = c->Rpad;
+  if (d->dtype == FIRP_BF16) {
+    c->Rwork = std::max(c->Rpad, std::min(FIRP_CHUNK_ROWS, (int)align_up(d->max_ctx, 16)));
+    c->part_elems = std::max(c->part_elems, (size_t)c->Rwork * (widest_layer + FIRP_PART_PAD) * 2);
+  }
 }
 
 #define HIPCHK(call)                                                                         \
@@ -340,7 +356,7 @@ Partial project(firp_ctx* c, const Act& in, const void* w, const void* w_packed,
                 int col, const Partial* like) {
   Partial out;
   out.ld = ld + FIRP_PART_PAD;
-  out.stride = (size_t)c->Rpad * out.ld;
+  out.stride = (rows <= c->Rpad ? (size_t)c->Rpad : align_up(rows, 16)) * out.ld;
   out.p = c->part;
   if (c->gemm_kind == 1 && w_packed && gemm_mfma_supported(rows, n, K)) {
     GemmPlan plan = gemm_mfma_plan(rows, n, K, like ? like->S : 0);
@@ -370,7 +386,7 @@ Partial project_stacked(firp_ctx* c, const Act& in, const void* w0, int n0, cons
   if (c->gemm_kind == 1 && w_packed && gemm_mfma_supported(rows, n, K)) {
     Partial out;
     out.ld = n + FIRP_PART_PAD;
-    out.stride = (size_t)c->Rpad * out.ld;
+    out.stride = (rows <= c->Rpad ? (size_t)c->Rpad : align_up(rows, 16)) * out.ld;
     out.p = c->part;
     GemmPlan plan = gemm_mfma_plan(rows, n, K, 0);
     if ((size_t)plan.S * out.stride > c->part_elems)
@@ -432,8 +448,11 @@ void ensure_packed(firp_ctx* c) {
 // `head`, ends with final norm, lm-head and argmax / top-b.
 // Only the maps [map_lo, map_hi) take part (all k of them in a decoding step, one in the
 // training forward); seq0 is the first sequence of the launch.
+// `chain_tok`: the rows are a prompt chunk of sequence seq0 with these tokens (DEVICE; B == 1, no
+// head, MFMA kernels): row i follows row i - 1, no row tables are read, and the last layer ends
+// with the chunk's K and V, which is all that a prefill leaves.
 firp_status forward(firp_ctx* c, int B, int N, int n_anchor, bool head, int max_ctx_now, int seq0, int map_lo,
-                    int map_hi) {
+                    int map_hi, const int* chain_tok = nullptr) {
   if (c->gemm_kind == 1) ensure_packed(c);
   const firp_model_desc& d = c->d;
   hipStream_t s = c->stream;
@@ -442,8 +461,9 @@ firp_status forward(firp_ctx* c, int B, int N, int n_anchor, bool head, int max_
   const int qd = d.n_q_heads * d.head_dim, kvd = d.n_kv_heads * d.head_dim;
   const int real_rows = B * N, n_anchor_rows = B * n_anchor;
   const int k_act = n_anchor > 0 ? map_hi - map_lo : 0;
-  launch_embed(c->embed, c->dtype, c->st.tok, real_rows, d.d_model, d.vocab, c->x, s);
-  launch_rope_table(rt, c->st.p0, real_rows + k_act * n_anchor_rows, d.head_dim, d.rope_base, c->rope_tab, s);
+  const bool chain = chain_tok != nullptr;
+  launch_embed(c->embed, c->dtype, chain ? chain_tok : c->st.tok, real_rows, d.d_model, d.vocab, c->x, s);
+  launch_rope_table(rt, c->st.p0, chain ? seq0 : -1, real_rows + k_act * n_anchor_rows, d.head_dim, d.rope_base, c->rope_tab, s);
   Partial pending{};  // projection output not yet added to the residual stream
   // 1/rms of the latest norm, applied by the kernel that consumes the projection behind it
   const RowScale rs{c->norm_ss, norm_pieces(d.d_model), 1.0f / (float)d.d_model, d.rms_eps};
@@ -507,7 +527,8 @@ firp_status forward(firp_ctx* c, int B, int N, int n_anchor, bool head, int max_
     if (c->attn_kind == 1 && sp) {
       launch_rope_kv_tiles(q, rs, d.n_q_heads, B, N, n_local - N, n_anchor, seq0, c->st.p0, c->rope_tab, c->q_frag, kv,
                            s);
-      launch_attention_mfma(c->q_frag, rows, d.n_q_heads, B, N, n_local - N, n_anchor, seq0, rt, c->st.p0, max_ctx_now,
+      if (chain && layer + 1 == d.n_layers) break;
+      launch_attention_mfma(c->q_frag, rows, d.n_q_heads, B, N, n_local - N, n_anchor, seq0, chain, rt, c->st.p0, max_ctx_now,
                             kv, c->attn_scratch, c->act_o, s);
     } else {
       launch_rope_kv(q, rs, rows, d.n_q_heads, rt, c->st.p0, c->rope_tab, c->act_q, sp, kv, c->dtype, s);
@@ -966,40 +987,49 @@ firp_status firp_prefill(firp_ctx* c, int32_t batch, const int32_t* tokens, cons
   }
   for (size_t i = 0; i < total; ++i)
     if (tokens[i] < 0 || tokens[i] >= c->d.vocab) return c->fail(FIRP_EINVAL, "token %zu = %d outside the vocabulary", i, tokens[i]);
-  int C = c->d.max_rows;
-  if (!(c->attn_kind == 1 && c->split) && (size_t)(c->d.head_dim + longest + C) * sizeof(float) > 64 * 1024)
+  if (!(c->attn_kind == 1 && c->split) && (size_t)(c->d.head_dim + longest + c->d.max_rows) * sizeof(float) > 64 * 1024)
     return c->fail(FIRP_ECAPACITY, "prompt of %d tokens exceeds the plain attention kernel's limit", longest);
   hipStream_t s = c->stream;
   c->prefilled = false;
   c->tables_valid = false;
   firp_status cst = ensure_cache_clean(c);
   if (cst != FIRP_OK) return cst;
-  // prompt[:-1] through the decoder in chunks: a chunk is a chain whose mask is lower-triangular
-  std::vector<int> seq(C), local(C), pos(C);
-  std::vector<unsigned long long> mask((size_t)C * FIRP_MASK_WORDS, 0);
-  for (int j = 0; j < C; ++j) {
-    local[j] = pos[j] = j;
-    for (int i = 0; i <= j; ++i) mask[(size_t)j * FIRP_MASK_WORDS + (i >> 6)] |= 1ull << (i & 63);
+  // prompt[:-1] through the decoder in chunks: a chunk is a chain whose mask is lower-triangular.
+  // The MFMA kernels take chunks of up to Rwork rows without row tables; the plain ones chunks of
+  // max_rows with the tables of the slot that is never cached.
+  const bool chain = c->attn_kind == 1 && c->split && c->gemm_kind == 1;
+  const int C = chain ? c->Rwork : c->d.max_rows;
+  std::vector<int> seq(C);
+  if (!chain) {
+    std::vector<int> local(C), pos(C);
+    std::vector<unsigned long long> mask((size_t)C * FIRP_MASK_WORDS, 0);
+    for (int j = 0; j < C; ++j) {
+      local[j] = pos[j] = j;
+      for (int i = 0; i <= j; ++i) mask[(size_t)j * FIRP_MASK_WORDS + (i >> 6)] |= 1ull << (i & 63);
+    }
+    select_slot(c, FIRP_TOPO_SLOTS);
+    HIPCHK(hipStreamSynchronize(s));
+    HIPCHK(hipMemcpy(c->rt_local, local.data(), C * sizeof(int), hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(c->rt_pos, pos.data(), C * sizeof(int), hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(c->rt_mask, mask.data(), mask.size() * sizeof(unsigned long long), hipMemcpyHostToDevice));
   }
-  select_slot(c, FIRP_TOPO_SLOTS);   // the chunk tables live in the slot that is never cached
-  HIPCHK(hipStreamSynchronize(s));
-  HIPCHK(hipMemcpy(c->rt_local, local.data(), C * sizeof(int), hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(c->rt_pos, pos.data(), C * sizeof(int), hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(c->rt_mask, mask.data(), mask.size() * sizeof(unsigned long long), hipMemcpyHostToDevice));
+  HIPCHK(hipMemcpyAsync(c->prompt_tok, tokens, total * sizeof(int), hipMemcpyHostToDevice, s));
   const int32_t* tk = tokens;
   for (int b = 0; b < batch; ++b) {
-    std::fill(seq.begin(), seq.end(), b);
-    HIPCHK(hipStreamSynchronize(s));
-    HIPCHK(hipMemcpy(c->rt_seq, seq.data(), C * sizeof(int), hipMemcpyHostToDevice));
+    if (!chain) {
+      std::fill(seq.begin(), seq.end(), b);
+      HIPCHK(hipStreamSynchronize(s));
+      HIPCHK(hipMemcpy(c->rt_seq, seq.data(), C * sizeof(int), hipMemcpyHostToDevice));
+    }
     launch_set_root(c->st, b, tk[lens[b] - 1], 0, s);
     int done = 0, todo = lens[b] - 1;
     while (done < todo) {
       int n = std::min(C, todo - done);
-      HIPCHK(hipMemcpyAsync(c->st.tok, tk + done, n * sizeof(int), hipMemcpyHostToDevice, s));
-      firp_status st = forward(c, 1, n, 0, false, done, b, 0, 0);
+      const int* dev_tok = c->prompt_tok + (tk - tokens) + done;
+      if (!chain) HIPCHK(hipMemcpyAsync(c->st.tok, dev_tok, n * sizeof(int), hipMemcpyDeviceToDevice, s));
+      firp_status st = forward(c, 1, n, 0, false, done, b, 0, 0, chain ? dev_tok : nullptr);
       if (st != FIRP_OK) return st;
       launch_advance_by(c->st.p0, b, n, s);
-      HIPCHK(hipStreamSynchronize(s));  // the token staging buffer is reused by the next chunk
       done += n;
     }
     c->p0[b] = todo;

@@ -58,8 +58,10 @@ void launch_add_rmsnorm(float* x, const Partial& part, int rows, int d, const vo
 // Only the residual update, no norm output (used before the projection at the FIRP layer).
 void launch_add_partial(float* x, const Partial& part, int rows, int d, hipStream_t s);
 // qkv partials -> rotary q (activation planes, [rows][Hq*dh]) and K / V^T into the cache.
-void launch_rope_table(const RowTab& rt, const int* p0, int rows, int head_dim, float rope_base,
-                       float2* tab, hipStream_t s);   // cos/sin of every row's position, once per step
+// cos/sin of every row's position, once per step; chain_seq >= 0: the rows are a prompt chunk of
+// that sequence (row i at position p0 + i) and the row tables are not read
+void launch_rope_table(const RowTab& rt, const int* p0, int chain_seq, int rows, int head_dim, float rope_base,
+                       float2* tab, hipStream_t s);
 void launch_rope_kv(const Partial& qkv, const RowScale& rs, int rows, int n_q_heads, const RowTab& rt, const int* p0,
                     const float2* tab, const Act& q_out, bool split, const KvView& kv, int dtype,
                     hipStream_t s);
@@ -99,11 +101,13 @@ void launch_attention_simple(const Act& q, bool split, int rows, int n_q_heads, 
 // per-split partial results (attention_mfma_scratch_floats floats).
 #define FIRP_ATTN_MAX_SPLITS 16
 bool attention_mfma_supported(int head_dim, int dtype);
-size_t attention_mfma_scratch_floats(int rows, int n_q_heads, int head_dim);
+#define FIRP_ATTN_CHUNK_SPLITS 4    // of a prompt chunk of more than one block of rows
+// rows: of a step; chunk_rows: of the largest prompt chunk
+size_t attention_mfma_scratch_floats(int rows, int chunk_rows, int n_q_heads, int head_dim);
 void launch_attention_mfma(const bf16* q_frag, int rows, int n_q_heads, int B, int n_real_per_seq,
-                           int n_pseudo_per_seq, int n_anchor_per_seq, int seq0, const RowTab& rt, const int* p0, int max_ctx_now,
-                           const KvView& kv, float* scratch, const Act& out, hipStream_t s);
-// (seq0: first sequence of the launch; a prefill chunk runs one sequence as a batch of one.)
+                           int n_pseudo_per_seq, int n_anchor_per_seq, int seq0, bool chain, const RowTab& rt, const int* p0,
+                           int max_ctx_now, const KvView& kv, float* scratch, const Act& out, hipStream_t s);
+// (seq0: first sequence of the launch; a prompt chunk (chain) runs one sequence as a batch of one.)
 // Its operand producer (replaces launch_rope_kv on this path): q as MFMA fragments in q_frag
 // (attention_q_frag_elems bf16 elements), K and V^T into the cache.
 size_t attention_q_frag_elems(int rows, int max_batch, int n_q_heads, int head_dim);

@@ -125,19 +125,20 @@ void launch_add_partial(float* x, const Partial& part, int rows, int d, hipStrea
 // one), then K and V^T go to cache slot p0 + local.  cos/sin come from a per-step table whose
 // angles are formed in fp64: at positions in the thousands an fp32 product would already be
 // off by 1e-4 rad.
-__global__ void k_rope_table(RowTab rt, const int* __restrict__ p0, int half, float rope_base, float2* tab) {
+__global__ void k_rope_table(RowTab rt, const int* __restrict__ p0, int chain_seq, int half, float rope_base, float2* tab) {
   int r = blockIdx.x, j = threadIdx.x;
   if (j >= half) return;
   double inv_freq = exp2(-(double)j / (double)half * log2((double)rope_base));
-  double ang = (double)(p0[rt.seq[r]] + rt.pos_off[r]) * inv_freq;
+  const int pos = chain_seq >= 0 ? p0[chain_seq] + r : p0[rt.seq[r]] + rt.pos_off[r];
+  double ang = (double)pos * inv_freq;
   double sd, cd;
   sincos(ang, &sd, &cd);
   tab[(size_t)r * half + j] = make_float2((float)cd, (float)sd);
 }
 
-void launch_rope_table(const RowTab& rt, const int* p0, int rows, int head_dim, float rope_base, float2* tab,
+void launch_rope_table(const RowTab& rt, const int* p0, int chain_seq, int rows, int head_dim, float rope_base, float2* tab,
                        hipStream_t s) {
-  hipLaunchKernelGGL(k_rope_table, dim3(rows), dim3(head_dim / 2), 0, s, rt, p0, head_dim / 2, rope_base, tab);
+  hipLaunchKernelGGL(k_rope_table, dim3(rows), dim3(head_dim / 2), 0, s, rt, p0, chain_seq, head_dim / 2, rope_base, tab);
 }
 
 // blockDim = (dh/2, heads per block); blockIdx = (row, head group)
