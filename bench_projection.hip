@@ -78,17 +78,14 @@ int main(int argc, char** argv) {
     CK(hipDeviceSynchronize());
     CK(hipFree(pool));
     int rp = (rows + 15) / 16 * 16;
-    unsigned short *xh, *xl;
-    CK(hipMalloc(&xh, (size_t)rp * sh.K * 2));
-    CK(hipMalloc(&xl, (size_t)rp * sh.K * 2));
-    hipLaunchKernelGGL(k_fill_bf16, dim3(512), dim3(256), 0, 0, xh, (size_t)rp * sh.K, 3u);
-    hipLaunchKernelGGL(k_fill_bf16, dim3(512), dim3(256), 0, 0, xl, (size_t)rp * sh.K, 5u);
+    unsigned short* xp;
+    CK(hipMalloc(&xp, (size_t)rp * act_row(sh.K) * 2));
+    hipLaunchKernelGGL(k_fill_bf16, dim3(512), dim3(256), 0, 0, xp, (size_t)rp * act_row(sh.K), 3u);
     GemmPlan plan = force_nw ? gemm_mfma_plan_ex(rows, sh.n, sh.K, force_s, force_nw) : gemm_mfma_plan(rows, sh.n, sh.K, force_s);
     float* part;
     CK(hipMalloc(&part, (size_t)plan.S * rp * sh.n * 4));
     Act a{};
-    a.hi = (bf16*)xh;
-    a.lo = (bf16*)xl;
+    a.pl = (bf16*)xp;
     a.ld = sh.K;
     auto run = [&](int i) {
       launch_gemm_mfma(a, packed + (size_t)(i % cnt) * pbytes, part, sh.n, (size_t)rp * sh.n, rows, sh.n, sh.K, plan, 0);
@@ -107,8 +104,7 @@ int main(int argc, char** argv) {
            rows, sh.n, sh.K, plan.S, plan.nw, plan.grid, us, wbytes / us / 1e3, wbytes / 1e6);
     fflush(stdout);
     CK(hipFree(packed));
-    CK(hipFree(xh));
-    CK(hipFree(xl));
+    CK(hipFree(xp));
     CK(hipFree(part));
   }
   return 0;

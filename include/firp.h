@@ -287,8 +287,8 @@ firp_status firp_debug_stream_read(const void *src, size_t bytes, void *sink, vo
 /* Host only: the launch plan the library picks for a projection of `rows` activation rows with an
  * [n, K] bf16 weight matrix (no device work; for tests of the planning logic).  Out (HOST, each may
  * be NULL): split-K factor, K elements per split (a multiple of 64), waves per workgroup (each owns
- * 32 rows of W), workgroups of one launch, and the activation rows one launch takes (128, or 256
- * when the kernel for 129..256 rows applies).  FIRP_EINVAL for a shape the MFMA kernels do not take
+ * 32 rows of W), workgroups of one launch (per row block), and the activation rows of a row block (128, or
+ * up to 256 where the kernel for more than 128 rows applies).  FIRP_EINVAL for a shape the MFMA kernels do not take
  * (rows < 1, n % 4 != 0, K % 8 != 0). */
 firp_status firp_debug_gemm_plan(int32_t rows, int32_t n, int32_t k_dim, int32_t *splits, int32_t *k_per_split,
                                  int32_t *waves, int32_t *grid, int32_t *row_block);

@@ -488,7 +488,7 @@ __global__ __launch_bounds__(64 * NWAVES, 1) void k_attention_mfma(const bf16* _
         const float inv = 1.0f / l;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
-          act_store4<true>(out, (size_t)row_of[p] * out.ld + (size_t)head_of[p] * DH + dt * 16 + 4 * kb, o[p][dt][0] * inv,
+          act_store4<true>(out, row_of[p], head_of[p] * DH + dt * 16 + 4 * kb, o[p][dt][0] * inv,
                            o[p][dt][1] * inv, o[p][dt][2] * inv, o[p][dt][3] * inv);
         continue;
       }
@@ -540,7 +540,7 @@ __global__ void k_attn_combine(const float* __restrict__ part_o, const float* __
       }
     }
   const float inv = 1.0f / L;
-  act_store4<SPLIT>(out, (size_t)r * out.ld + (size_t)h * dh + d, acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+  act_store4<SPLIT>(out, r, h * dh + d, acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
 }
 
 bool attention_mfma_supported(int head_dim, int dtype) {

@@ -7,11 +7,13 @@
 namespace firp {
 
 template <bool SPLIT>
-__device__ __forceinline__ float act_load(const Act& a, size_t idx) {
-  if constexpr (SPLIT)
-    return to_f32(a.hi[idx]) + to_f32(a.lo[idx]);
-  else
-    return a.f32[idx];
+__device__ __forceinline__ float act_load(const Act& a, int row, int col) {
+  if constexpr (SPLIT) {
+    const bf16* p = act_at(a, row, col);
+    return to_f32(p[0]) + to_f32(p[32]);
+  } else {
+    return a.f32[(size_t)row * a.ld + col];
+  }
 }
 
 template <typename KT, bool SPLIT>
@@ -30,7 +32,7 @@ __global__ __launch_bounds__(256) void k_attention_simple(Act q, int n_q_heads, 
   const KT* K = (const KT*)kv.k + (size_t)b * kv.seq_stride + (size_t)hk * kv.slots * dh;
   const KT* Vt = (const KT*)kv.v + (size_t)b * kv.seq_stride + (size_t)hk * dh * kv.slots;
   const unsigned long long* mask = rt.mask + (size_t)r * FIRP_MASK_WORDS;
-  for (int i = tid; i < dh; i += 256) qs[i] = act_load<SPLIT>(q, (size_t)r * q.ld + (size_t)h * dh + i);
+  for (int i = tid; i < dh; i += 256) qs[i] = act_load<SPLIT>(q, r, h * dh + i);
   __syncthreads();
   int nkeys = ctx + n_local;
   float scale = 1.0f / sqrtf((float)dh);
@@ -64,7 +66,7 @@ __global__ __launch_bounds__(256) void k_attention_simple(Act q, int n_q_heads, 
     const KT* vr = Vt + (size_t)d * kv.slots;
     float o = 0.f;
     for (int j = 0; j < nkeys; ++j) o += sc[j] * to_f32(vr[j]);
-    act_store<SPLIT>(out, (size_t)r * out.ld + (size_t)h * dh + d, o * inv);
+    act_store<SPLIT>(out, r, h * dh + d, o * inv);
   }
 }
 

@@ -42,36 +42,47 @@ __device__ __forceinline__ void store_elt<bf16>(bf16* p, float v) { *p = f32_to_
 // ---- activations handed to a projection -----------------------------------------------------
 // fp32 models keep activations in fp32.  bf16 models hand the MFMA kernel two bf16 planes,
 // hi = rne(v) and lo = rne(v - hi): together they carry ~16 mantissa bits, so rounding the
-// activations costs no accuracy while both MFMA operands stay bf16.
+// activations costs no accuracy while both MFMA operands stay bf16.  The planes are interleaved
+// by 32 columns: a row is [32 hi][32 lo][32 hi][32 lo]..., so that the 32 columns of one MFMA step are
+// one whole 128-byte line per row in both planes together, and a kernel may stage 32 columns at
+// a time without fetching half lines.
 struct Act {
   float* f32;  // [rows][ld] or nullptr
-  bf16* hi;    // [rows][ld] or nullptr
-  bf16* lo;
-  int ld;
+  bf16* pl;    // [rows][act_row(ld)] or nullptr
+  int ld;      // columns
 };
+// bf16 elements of a row of planes (a last group of fewer than 32 columns is padded; nobody writes the
+// padding, and readers must not use it)
+__host__ __device__ __forceinline__ int act_row(int ld) { return (ld + 31) / 32 * 64; }
+// element of column `col` in the hi plane; the lo plane's is 32 further
+__device__ __forceinline__ bf16* act_at(const Act& a, int row, int col) {
+  return a.pl + (size_t)row * act_row(a.ld) + (col >> 5) * 64 + (col & 31);
+}
 
 template <bool SPLIT>
-__device__ __forceinline__ void act_store(const Act& a, size_t idx, float v) {
+__device__ __forceinline__ void act_store(const Act& a, int row, int col, float v) {
   if constexpr (SPLIT) {
     bf16 h = f32_to_bf16(v);
-    a.hi[idx] = h;
-    a.lo[idx] = f32_to_bf16(v - to_f32(h));
+    bf16* p = act_at(a, row, col);
+    p[0] = h;
+    p[32] = f32_to_bf16(v - to_f32(h));
   } else {
-    a.f32[idx] = v;
+    a.f32[(size_t)row * a.ld + col] = v;
   }
 }
 
-// four consecutive activations (idx % 4 == 0): one 8-byte store per plane
+// four consecutive activations (col % 4 == 0): one 8-byte store per plane
 template <bool SPLIT>
-__device__ __forceinline__ void act_store4(const Act& a, size_t idx, float v0, float v1, float v2, float v3) {
+__device__ __forceinline__ void act_store4(const Act& a, int row, int col, float v0, float v1, float v2, float v3) {
   if constexpr (SPLIT) {
     uint2 ph, pl;
     split2_bf16(v0, v1, ph.x, pl.x);
     split2_bf16(v2, v3, ph.y, pl.y);
-    *(uint2*)(a.hi + idx) = ph;
-    *(uint2*)(a.lo + idx) = pl;
+    bf16* p = act_at(a, row, col);
+    *(uint2*)p = ph;
+    *(uint2*)(p + 32) = pl;
   } else {
-    *(float4*)(a.f32 + idx) = make_float4(v0, v1, v2, v3);
+    *(float4*)(a.f32 + (size_t)row * a.ld + col) = make_float4(v0, v1, v2, v3);
   }
 }
 

@@ -214,8 +214,7 @@ size_t carve(firp_ctx* c, char* base) {
   auto act = [&](Act& a, int ld) {
     a.ld = ld;
     a.f32 = cv.take<float>((size_t)Rp * ld);
-    a.hi = cv.take<bf16>((size_t)Rw * ld);
-    a.lo = cv.take<bf16>((size_t)Rw * ld);
+    a.pl = cv.take<bf16>((size_t)Rw * act_row(ld));
   };
   act(c->act_d, d.d_model);
   act(c->act_q, qd);
@@ -368,7 +367,7 @@ Partial project(firp_ctx* c, const Act& in, const void* w, const void* w_packed,
     if (timed) {
       (void)hipEventRecord(c->ev[c->ev_used++], c->stream);
       c->gemm_bytes += 2.0 * (double)n * (double)K;
-      c->gemm_launches += (rows + plan.row_block - 1) / plan.row_block;
+      c->gemm_launches += plan.xt ? 1 : (rows + plan.row_block - 1) / plan.row_block;
     }
     out.S = plan.S;
   } else {
@@ -397,7 +396,7 @@ Partial project_stacked(firp_ctx* c, const Act& in, const void* w0, int n0, cons
     if (timed) {
       (void)hipEventRecord(c->ev[c->ev_used++], c->stream);
       c->gemm_bytes += 2.0 * (double)n * (double)K;
-      c->gemm_launches += (rows + plan.row_block - 1) / plan.row_block;
+      c->gemm_launches += plan.xt ? 1 : (rows + plan.row_block - 1) / plan.row_block;
     }
     out.S = plan.S;
     return out;
@@ -1337,13 +1336,16 @@ static void gemm_in_workspace(const float* x, const void* w, float* y, int rows,
   size_t rp = align_up(rows, 16);
   Act a{};
   a.ld = k_dim;
-  a.hi = (bf16*)workspace;
-  a.lo = a.hi + rp * k_dim;
-  float* part = (float*)((char*)workspace + align_up(rp * k_dim * 2 * 2, 256));
-  void* wpk = (char*)part + align_up(rp * (size_t)n * 4 * 16, 256);
+  a.pl = (bf16*)workspace;
+  float* part = (float*)((char*)workspace + align_up(rp * act_row(k_dim) * 2, 256));
+  char* end = (char*)workspace + firp_gemm_workspace_bytes(rows, n, k_dim) - 512;
+  void* wpk = end - align_up(gemm_packed_bytes(n, k_dim), 256);
   launch_split_act(x, rows, k_dim, a, s);
   launch_pack_weights(wseg1(w, n), n, k_dim, wpk, s);
   GemmPlan plan = gemm_mfma_plan(rows, n, k_dim, 0);
+  // (the rows of planes of a K that is no multiple of 32 are longer than the size says: they take their
+  // last bytes from the sixteenth split's room)
+  while (plan.S > 1 && (char*)(part + plan.S * rp * (size_t)n) > (char*)wpk) plan = gemm_mfma_plan(rows, n, k_dim, plan.S - 1);
   launch_gemm_mfma(a, wpk, part, n, rp * n, rows, n, k_dim, plan, s);
   launch_reduce_partials(Partial{part, plan.S, rp * (size_t)n, n}, y, rows, s);
 }

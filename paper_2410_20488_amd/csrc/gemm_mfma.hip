@@ -3,9 +3,9 @@
 
 namespace firp {
 
-// the kernel for 129..256 rows (gemm_tall.hip); takes K % 64 == 0 only
-void launch_gemm_tall(const bf16* xhi, const bf16* xlo, int ldx, int rows, const void* w_packed, int n, int K,
-                      float* out, int ld, size_t part_stride, const GemmPlan& plan, hipStream_t s);
+// the kernel for more than 128 rows (gemm_tall.hip); takes K % 64 == 0 only
+void launch_gemm_tall(const bf16* x, int ldx, int rows, const void* w_packed, int n, int K, float* out, int ld,
+                      size_t part_stride, const GemmPlan& plan, hipStream_t s);
 static bool tall_shape(int rows, int K) { return rows > 128 && K % 64 == 0; }
 
 bool gemm_mfma_supported(int rows, int n, int K) {
@@ -33,8 +33,51 @@ GemmPlan gemm_mfma_plan_ex(int rows, int n, int K, int S, int nw) {
   p.S = S;  // splits past the end of K find no stage and leave zeros
   p.k_per = per * KC;
   p.grid = tiles * p.S;
-  p.row_block = (tall_shape(rows, K) && (nw == 8 || nw == 6)) ? 256 : 128;
+  p.xt = tall_shape(rows, K) && (nw == 8 || nw == 6) ? (rows <= 192 ? 3 : 4) : 0;
+  p.row_block = p.xt ? 256 : 128;
   return p;
+}
+
+// The plan of the kernel for more than 128 rows: tile (32 nw rows of W x 64 xt rows of X) and split
+// factor by the time of its fullest CU, in microseconds:
+//   rounds x stages per workgroup x time of a stage   one workgroup per CU (they fill its registers), so
+//                                    the grid runs in whole rounds of 256; a 256 x 256 stage takes 2.6
+//                                    (two thirds of the matrix units' nominal rate), the smaller tiles as much
+//                                    longer than their share of it as the constants say, and with one row block
+//                                    none is faster than its weights arrive from HBM (2.2 for 256 rows)
+//   + 6                              launch, first loads, last stores
+//   + the partial sums written at 5 and read by the consumer at 4 TB/s
+// The constants come from launches measured over (nw, xt, S) at the LLaMA-2 7B, 13B and 34B shapes with
+// 160 to 2048 rows.
+static GemmPlan tall_plan(int rows, int n, int K, int force_split) {
+  const int stages = K / KC;
+  struct Tile { int nw, xt; double us; };
+  const Tile tile[] = {{8, 4, 2.6}, {6, 4, 2.15}, {8, 3, 1.93}, {6, 3, 1.75}, {6, 5, 2.55}};
+  GemmPlan best{};
+  double best_us = -1.0;
+  bool best_busy = false;
+  for (const Tile& t : tile) {
+    const int tiles = (n + 32 * t.nw - 1) / (32 * t.nw), blocks = (rows + 64 * t.xt - 1) / (64 * t.xt);
+    if (rows <= 256 && blocks > 1) continue;   // one pass over W
+    const double stage_us = blocks == 1 ? std::max(t.us, 0.275 * t.nw) : t.us;
+    const int s_lo = force_split > 0 ? force_split : 1, s_hi = force_split > 0 ? force_split : 16;
+    for (int S = s_lo; S <= s_hi; ++S) {
+      if (force_split <= 0 && S > 1 && stages / S < 4) break;
+      const long wgs = (long)tiles * blocks * S, rounds = (wgs + 255) / 256;
+      if (force_split <= 0 && S > 1 && rounds > 1) break;   // more splits than fill the chip only add partial sums
+      const int per = (stages + std::min(S, stages) - 1) / std::min(S, stages);
+      const bool busy = wgs >= 170;   // two thirds of the CUs: fewer cannot pull the weights at the chip's rate
+      if (best_us >= 0.0 && best_busy && !busy) continue;
+      const double us = rounds * per * stage_us + 6.0 + (double)S * rows * n * 4.0 * (1 / 5.0e6 + 1 / 4.0e6);
+      if (best_us < 0.0 || (busy && !best_busy) || us < best_us - 1e-9) {
+        best_us = us;
+        best_busy = busy;
+        best = gemm_mfma_plan_ex(rows, n, K, S, t.nw);
+        best.xt = t.xt;
+      }
+    }
+  }
+  return best;
 }
 
 // A CU moves data at a capped rate however many workgroups it holds (its vector cache keeps only
@@ -52,7 +95,7 @@ GemmPlan gemm_mfma_plan_ex(int rows, int n, int K, int S, int nw) {
 static double plan_cost(int rows, int n, int K, int S, int nw, int nt) {
   const int stages = (K + KC - 1) / KC;
   const int per = (stages + S - 1) / S;
-  const int r = std::min(rows, 256);
+  const int r = std::min(rows, 128);
   return per * (nw + 0.6 * nt) + r * nw / 32.0 + 6.0 * std::max(0, 8 - per)
          + (double)S * r * n / 262144.0;   // and the consumer reads every partial sum back (spread over 256 CUs)
 }
@@ -60,13 +103,12 @@ static double plan_cost(int rows, int n, int K, int S, int nw, int nt) {
 GemmPlan gemm_mfma_plan(int rows, int n, int K, int force_split) {
   const int stages = (K + KC - 1) / KC;
   const int n_cu = 256;
-  const bool tall = tall_shape(rows, K);   // the 8-wave kernel for 129..256 rows per pass
-  const int nt = tall ? (std::min(rows, 256) + 15) / 16 : pick_nt(rows);
-  const int nw_hi = 8, nw_lo = tall ? 6 : std::min(4, std::max(2, nt));
+  if (tall_shape(rows, K)) return tall_plan(rows, n, K, force_split);
+  const int nt = pick_nt(rows);
+  const int nw_hi = 8, nw_lo = std::min(4, std::max(2, nt));
   int best_nw = nw_hi, best_S = std::max(1, force_split);
   double best = -1.0;
   for (int nw = nw_hi; nw >= nw_lo; --nw) {
-    if (tall && nw == 7) continue;   // that kernel's workgroups own 256 or 192 rows of W
     int tiles = (n + nw * 32 - 1) / (nw * 32);
     int s_lo = force_split > 0 ? force_split : 1, s_hi = force_split > 0 ? force_split : 16;
     for (int S = s_lo; S <= s_hi; ++S) {
@@ -123,28 +165,28 @@ void launch_pack_weights(const WSeg& src, int n, int K, void* dst, hipStream_t s
 
 void launch_gemm_mfma(const Act& x, const void* w_packed, float* out, int ld, size_t part_stride, int rows, int n,
                       int K, const GemmPlan& plan, hipStream_t s) {
+  const char* w = (const char*)w_packed;
+  const int ldx = act_row(x.ld);
+  if (plan.xt) {
+    launch_gemm_tall(x.pl, ldx, rows, w, n, K, out, ld, part_stride, plan, s);
+    return;
+  }
   // more rows than one pass takes: row blocks (W is streamed once per block)
   const int block = plan.row_block;
   for (int r0 = 0; r0 < rows; r0 += block) {
     int rb = std::min(block, rows - r0);
     GemmPlan p = plan;
     p.nt = pick_nt(rb);
-    const bf16* xhi = x.hi + (size_t)r0 * x.ld;
-    const bf16* xlo = x.lo + (size_t)r0 * x.ld;
+    const bf16* xr = x.pl + (size_t)r0 * ldx;
     float* o = out + (size_t)r0 * ld;
-    const char* w = (const char*)w_packed;
-    if (rb > 128) {
-      launch_gemm_tall(xhi, xlo, x.ld, rb, w, n, K, o, ld, part_stride, p, s);
-      continue;
-    }
     switch (p.nw) {
-      case 2: launch_gemm_mfma_nw<2>(xhi, xlo, x.ld, rb, w, n, K, o, ld, part_stride, p, s); break;
-      case 3: launch_gemm_mfma_nw<3>(xhi, xlo, x.ld, rb, w, n, K, o, ld, part_stride, p, s); break;
-      case 4: launch_gemm_mfma_nw<4>(xhi, xlo, x.ld, rb, w, n, K, o, ld, part_stride, p, s); break;
-      case 5: launch_gemm_mfma_nw<5>(xhi, xlo, x.ld, rb, w, n, K, o, ld, part_stride, p, s); break;
-      case 6: launch_gemm_mfma_nw<6>(xhi, xlo, x.ld, rb, w, n, K, o, ld, part_stride, p, s); break;
-      case 7: launch_gemm_mfma_nw<7>(xhi, xlo, x.ld, rb, w, n, K, o, ld, part_stride, p, s); break;
-      default: launch_gemm_mfma_nw<8>(xhi, xlo, x.ld, rb, w, n, K, o, ld, part_stride, p, s); break;
+      case 2: launch_gemm_mfma_nw<2>(xr, ldx, rb, w, n, K, o, ld, part_stride, p, s); break;
+      case 3: launch_gemm_mfma_nw<3>(xr, ldx, rb, w, n, K, o, ld, part_stride, p, s); break;
+      case 4: launch_gemm_mfma_nw<4>(xr, ldx, rb, w, n, K, o, ld, part_stride, p, s); break;
+      case 5: launch_gemm_mfma_nw<5>(xr, ldx, rb, w, n, K, o, ld, part_stride, p, s); break;
+      case 6: launch_gemm_mfma_nw<6>(xr, ldx, rb, w, n, K, o, ld, part_stride, p, s); break;
+      case 7: launch_gemm_mfma_nw<7>(xr, ldx, rb, w, n, K, o, ld, part_stride, p, s); break;
+      default: launch_gemm_mfma_nw<8>(xr, ldx, rb, w, n, K, o, ld, part_stride, p, s); break;
     }
   }
 }

@@ -11,7 +11,7 @@
 //    vector cache tracks few outstanding lines per CU and stalls on exactly that pattern.
 //    Loads for three stages ahead are in flight while the current one is multiplied;
 //  * the activations are the small operand: a stage's [16*NT rows][64 k] tile of both planes
-//    (hi and lo bf16, see Act) is staged once per workgroup through LDS (double-buffered,
+//    (hi and lo bf16, interleaved, see Act) is staged once per workgroup through LDS (double-buffered,
 //    128-byte rows with the 16-byte pieces XOR-swizzled by the row number) and shared by
 //    the workgroup's waves;
 //  * fp32 accumulation in the MFMA accumulators; rows of X beyond `rows` and rows of W beyond
@@ -38,8 +38,7 @@ __device__ __forceinline__ bf16x8_t as_bf16x8(u32x4_t v) { return __builtin_bit_
 }  // namespace
 
 template <int NT, int MT, bool KTAIL, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void k_gemm_mfma(const bf16* __restrict__ xhi, const bf16* __restrict__ xlo,
-                                                      int ldx, int rows, const char* __restrict__ wpk, int n, int K,
+__global__ __launch_bounds__(64 * NW, 2) void k_gemm_mfma(const bf16* __restrict__ xpl, int ldx, int rows, const char* __restrict__ wpk, int n, int K,
                                                       float* __restrict__ out, int ld_out, size_t part_stride,
                                                       int S, int k_per, int tiles) {
   constexpr int XROWS = NT * 16;
@@ -64,7 +63,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_gemm_mfma(const bf16* __restrict
     const int t16 = min((n0 >> 4) + mt, n16 - 1);
     wp[mt] = wpk + ((size_t)t16 * kp32 + (k_begin >> 5)) * 1024 + lane * 16;
   }
-  // X: the stage tile is 2 planes x XROWS rows x 8 chunks of 16 B; chunk id -> thread round-robin
+  // X (ldx: bf16 elements of a row of planes): the stage tile is XROWS rows x 16 pieces of 16 B, two
+  // lines of [32 hi][32 lo]; piece id -> thread round-robin
   constexpr int XCHUNKS = 2 * XROWS * 8;
   constexpr int XP = (XCHUNKS + 64 * NW - 1) / (64 * NW);  // loads per thread per stage
   const char* xp[XP];
@@ -72,15 +72,16 @@ __global__ __launch_bounds__(64 * NW, 2) void k_gemm_mfma(const bf16* __restrict
 #pragma unroll
   for (int i = 0; i < XP; ++i) {
     int c = min(tid + i * 64 * NW, XCHUNKS - 1);   // the clamp makes surplus threads repeat a chunk
-    int plane = c / (XROWS * 8), xrow = (c % (XROWS * 8)) >> 3;
+    const int xrow = c >> 4, plane = (c >> 2) & 1, piece = ((c >> 3) & 1) * 4 + (c & 3);
     int row = min(xrow, rows - 1);
-    xp[i] = (const char*)(plane ? xlo : xhi) + ((size_t)row * ldx + k_begin) * 2 + (c & 7) * 16;
-    xlds[i] = plane * PLANE + xrow * PITCH + (((c & 7) ^ (xrow & 7)) * 16);
-    xck[i] = c & 7;
+    xp[i] = (const char*)xpl + ((size_t)row * ldx + 2 * k_begin) * 2 + (c & 15) * 16;
+    xlds[i] = plane * PLANE + xrow * PITCH + ((piece ^ (xrow & 7) ^ (plane * 4)) * 16);
+    xck[i] = piece;
   }
-  // 16-byte piece p of row r sits at slot p ^ (r % 8) of the row: the fragment reads (16 rows x one
-  // piece per k-block) and the staging writes (8 pieces of a row per 8 lanes) are both free of
-  // bank conflicts, which padded rows are not (measured: 144-byte rows read at half the rate)
+  // 16-byte piece p of row r sits at slot p ^ (r % 8) of the row in the hi plane and at the slot in the
+  // other half in the lo plane: the fragment reads (16 rows x one piece per k-block) and the
+  // staging writes (4 pieces of a row in both planes per 8 lanes) are both free of bank conflicts,
+  // which padded rows are not (measured: 144-byte rows read at half the rate)
   const int blds = r16 * PITCH + ((kb ^ (r16 & 7)) * 16);
 
   // (the padding of the copy is zero, so the last stage of a ragged K needs no guard here)
@@ -96,9 +97,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_gemm_mfma(const bf16* __restrict
     for (int i = 0; i < XP; ++i) {
       if constexpr (KTAIL) {
         bool ok = k_begin + stage * KC + xck[i] * 8 < k_end;
-        x[i] = ok ? *(const u32x4_t*)(xp[i] + (size_t)stage * (KC * 2)) : u32x4_t{0, 0, 0, 0};
+        x[i] = ok ? *(const u32x4_t*)(xp[i] + (size_t)stage * (KC * 4)) : u32x4_t{0, 0, 0, 0};
       } else {
-        x[i] = *(const u32x4_t*)(xp[i] + (size_t)stage * (KC * 2));
+        x[i] = *(const u32x4_t*)(xp[i] + (size_t)stage * (KC * 4));
       }
     }
   };
@@ -147,9 +148,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_gemm_mfma(const bf16* __restrict
       bf16x8_t bh[NT], bl[NT];
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
-        const unsigned char* bp = buf + (blds ^ (j * 64)) + nt * 16 * PITCH;
-        bh[nt] = as_bf16x8(*(const u32x4_t*)bp);
-        bl[nt] = as_bf16x8(*(const u32x4_t*)(bp + PLANE));
+        const unsigned char* bp = buf + nt * 16 * PITCH;
+        bh[nt] = as_bf16x8(*(const u32x4_t*)(bp + (blds ^ (j * 64))));
+        bl[nt] = as_bf16x8(*(const u32x4_t*)(bp + PLANE + (blds ^ ((j ^ 1) * 64))));
       }
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
@@ -189,33 +190,34 @@ __global__ __launch_bounds__(64 * NW, 2) void k_gemm_mfma(const bf16* __restrict
 
 
 // One translation unit per workgroup size instantiates this for every activation tile count.
+// (ldx: bf16 elements of a row of planes)
 template <int NW>
-void launch_gemm_mfma_nw(const bf16* xhi, const bf16* xlo, int ldx, int rows, const char* w, int n, int K, float* out,
-                         int ld, size_t part_stride, const GemmPlan& p, hipStream_t s);
+void launch_gemm_mfma_nw(const bf16* x, int ldx, int rows, const char* w, int n, int K, float* out, int ld,
+                         size_t part_stride, const GemmPlan& p, hipStream_t s);
 
 #define FIRP_GEMM_INSTANTIATE(NW)                                                                                     \
   template <int NT>                                                                                                   \
-  static void launch_nt_(const bf16* xhi, const bf16* xlo, int ldx, int rows, const char* w, int n, int K, float* out,\
-                         int ld, size_t part_stride, const GemmPlan& p, hipStream_t s) {                              \
+  static void launch_nt_(const bf16* x, int ldx, int rows, const char* w, int n, int K, float* out, int ld,           \
+                         size_t part_stride, const GemmPlan& p, hipStream_t s) {                                      \
     dim3 g((p.grid + 7) & ~7), b(64 * NW);                                                                            \
     if (K % KC)                                                                                                       \
-      hipLaunchKernelGGL((k_gemm_mfma<NT, 2, true, NW>), g, b, 0, s, xhi, xlo, ldx, rows, w, n, K, out, ld,           \
-                         part_stride, p.S, p.k_per, p.grid / p.S);                                                    \
+      hipLaunchKernelGGL((k_gemm_mfma<NT, 2, true, NW>), g, b, 0, s, x, ldx, rows, w, n, K, out, ld, part_stride,     \
+                         p.S, p.k_per, p.grid / p.S);                                                                 \
     else                                                                                                              \
-      hipLaunchKernelGGL((k_gemm_mfma<NT, 2, false, NW>), g, b, 0, s, xhi, xlo, ldx, rows, w, n, K, out, ld,          \
-                         part_stride, p.S, p.k_per, p.grid / p.S);                                                    \
+      hipLaunchKernelGGL((k_gemm_mfma<NT, 2, false, NW>), g, b, 0, s, x, ldx, rows, w, n, K, out, ld, part_stride,    \
+                         p.S, p.k_per, p.grid / p.S);                                                                 \
   }                                                                                                                   \
   template <>                                                                                                         \
-  void launch_gemm_mfma_nw<NW>(const bf16* xhi, const bf16* xlo, int ldx, int rows, const char* w, int n, int K,      \
-                               float* out, int ld, size_t part_stride, const GemmPlan& p, hipStream_t s) {            \
+  void launch_gemm_mfma_nw<NW>(const bf16* x, int ldx, int rows, const char* w, int n, int K, float* out, int ld,     \
+                               size_t part_stride, const GemmPlan& p, hipStream_t s) {                                \
     switch (p.nt) {                                                                                                   \
-      case 1: launch_nt_<1>(xhi, xlo, ldx, rows, w, n, K, out, ld, part_stride, p, s); break;                         \
-      case 2: launch_nt_<2>(xhi, xlo, ldx, rows, w, n, K, out, ld, part_stride, p, s); break;                         \
-      case 3: launch_nt_<3>(xhi, xlo, ldx, rows, w, n, K, out, ld, part_stride, p, s); break;                         \
-      case 4: launch_nt_<4>(xhi, xlo, ldx, rows, w, n, K, out, ld, part_stride, p, s); break;                         \
-      case 5: launch_nt_<5>(xhi, xlo, ldx, rows, w, n, K, out, ld, part_stride, p, s); break;                         \
-      case 6: launch_nt_<6>(xhi, xlo, ldx, rows, w, n, K, out, ld, part_stride, p, s); break;                         \
-      default: launch_nt_<8>(xhi, xlo, ldx, rows, w, n, K, out, ld, part_stride, p, s); break;                        \
+      case 1: launch_nt_<1>(x, ldx, rows, w, n, K, out, ld, part_stride, p, s); break;                                \
+      case 2: launch_nt_<2>(x, ldx, rows, w, n, K, out, ld, part_stride, p, s); break;                                \
+      case 3: launch_nt_<3>(x, ldx, rows, w, n, K, out, ld, part_stride, p, s); break;                                \
+      case 4: launch_nt_<4>(x, ldx, rows, w, n, K, out, ld, part_stride, p, s); break;                                \
+      case 5: launch_nt_<5>(x, ldx, rows, w, n, K, out, ld, part_stride, p, s); break;                                \
+      case 6: launch_nt_<6>(x, ldx, rows, w, n, K, out, ld, part_stride, p, s); break;                                \
+      default: launch_nt_<8>(x, ldx, rows, w, n, K, out, ld, part_stride, p, s); break;                               \
     }                                                                                                                 \
   }
 

@@ -126,7 +126,8 @@ struct GemmPlan {
   int nt;       // 16-row activation tiles of one pass of the streaming kernel (up to 8)
   int nw;       // waves per workgroup (each owns 32 rows of W): 2..8
   int grid;
-  int row_block;  // activation rows one launch takes: 128, or 256 (the kernel for 129..256 rows)
+  int row_block;  // activation rows of a pass over W: 128, or 256 (the kernel for more than 128 rows; one launch takes all)
+  int xt;         // of that kernel: its workgroups take 64 * xt activation rows (3..5); 0: the streaming kernel
 };
 GemmPlan gemm_mfma_plan_ex(int rows, int n, int K, int S, int nw);
 bool gemm_mfma_supported(int rows, int n, int K);

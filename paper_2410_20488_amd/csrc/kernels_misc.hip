@@ -83,7 +83,7 @@ __global__ __launch_bounds__(256) void k_add_rmsnorm(float* x, Partial part, int
     }
     if constexpr (NORM) {
       ss = a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w;
-      act_store4<SPLIT>(out, (size_t)r * out.ld + (size_t)i * 4, a.x * to_f32(gain[i * 4 + 0]),
+      act_store4<SPLIT>(out, r, i * 4, a.x * to_f32(gain[i * 4 + 0]),
                         a.y * to_f32(gain[i * 4 + 1]), a.z * to_f32(gain[i * 4 + 2]), a.w * to_f32(gain[i * 4 + 3]));
     }
   }
@@ -157,8 +157,8 @@ __global__ void k_rope_kv(Partial qkv, RowScale rs, int n_q_heads, RowTab rt, co
     float2 cs = tab[(size_t)r * half + j];
     float y1 = x1 * cs.x - x2 * cs.y, y2 = x2 * cs.x + x1 * cs.y;
     if (h < n_q_heads) {
-      act_store<SPLIT>(q_out, (size_t)r * q_out.ld + (size_t)h * dh + j, y1);
-      act_store<SPLIT>(q_out, (size_t)r * q_out.ld + (size_t)h * dh + j + half, y2);
+      act_store<SPLIT>(q_out, r, h * dh + j, y1);
+      act_store<SPLIT>(q_out, r, h * dh + j + half, y2);
     } else {
       int hk = h - n_q_heads;
       size_t slot = (size_t)(p0[b] + rt.local[r]);
@@ -221,7 +221,7 @@ __global__ void k_swiglu(Partial gu, RowScale rs, int F, Act out) {
   const float scale = row_scale(rs, r);
   g.x *= scale; g.y *= scale; g.z *= scale; g.w *= scale;
   u.x *= scale; u.y *= scale; u.z *= scale; u.w *= scale;
-  act_store4<SPLIT>(out, (size_t)r * out.ld + j, g.x / (1.0f + expf(-g.x)) * u.x, g.y / (1.0f + expf(-g.y)) * u.y,
+  act_store4<SPLIT>(out, r, j, g.x / (1.0f + expf(-g.x)) * u.x, g.y / (1.0f + expf(-g.y)) * u.y,
                     g.z / (1.0f + expf(-g.z)) * u.z, g.w / (1.0f + expf(-g.w)) * u.w);
 }
 
@@ -241,7 +241,7 @@ template <bool SPLIT>
 __global__ void k_gather_rows(const float* __restrict__ x, const int* __restrict__ src, int d, Act out) {
   int g = blockIdx.x;
   const float* xr = x + (size_t)src[g] * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) act_store<SPLIT>(out, (size_t)g * out.ld + i, xr[i]);
+  for (int i = threadIdx.x; i < d; i += blockDim.x) act_store<SPLIT>(out, g, i, xr[i]);
 }
 
 void launch_gather_rows(const float* x, const int* src_rows, int rows, int d, const Act& out,
@@ -572,7 +572,7 @@ void launch_set_root(const SeqState& st, int seq, int token, int p0, hipStream_t
 // helpers of the standalone projection entry
 __global__ void k_split_act(const float* __restrict__ x, int ld, Act out) {
   int r = blockIdx.x;
-  for (int i = threadIdx.x; i < ld; i += blockDim.x) act_store<true>(out, (size_t)r * out.ld + i, x[(size_t)r * ld + i]);
+  for (int i = threadIdx.x; i < ld; i += blockDim.x) act_store<true>(out, r, i, x[(size_t)r * ld + i]);
 }
 void launch_split_act(const float* x, int rows, int ld, const Act& out, hipStream_t s) {
   hipLaunchKernelGGL(k_split_act, dim3(rows), dim3(256), 0, s, x, ld, out);
