@@ -110,20 +110,20 @@ __device__ __forceinline__ float partial_sum(const Partial& q, size_t idx) {
 }
 
 // ---- row scale of an RMSNorm, applied after the projection --------------------------------
-// The norm kernel hands the projection x * gain and leaves the sum of squares of every row in P
+// The norm hands the projection x * gain and leaves the sum of squares of every row in P
 // pieces; the projection is linear, so the consumer of its output multiplies by
 // 1 / sqrt(mean(x^2) + eps) instead.  This lets the norm run on several workgroups per row
 // without a second pass.  ss == nullptr: no scale.
 struct RowScale {
-  const float* ss;   // [rows][FIRP_NORM_PIECES]
-  int pieces;
+  const float* ss;   // [rows][stride]
+  int pieces, stride;
   float inv_d, eps;
 };
 #define FIRP_NORM_PIECES 8
 __device__ __forceinline__ float row_scale(const RowScale& rs, int r) {
   if (!rs.ss) return 1.0f;
   float t = 0.f;
-  for (int p = 0; p < rs.pieces; ++p) t += rs.ss[(size_t)r * FIRP_NORM_PIECES + p];
+  for (int p = 0; p < rs.pieces; ++p) t += rs.ss[(size_t)r * rs.stride + p];
   return 1.0f / sqrtf(t * rs.inv_d + rs.eps);
 }
 

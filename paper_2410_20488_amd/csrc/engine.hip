@@ -95,6 +95,7 @@ struct firp_ctx {
   void* argmax_scratch = nullptr;
   bf16* q_frag = nullptr;      // q of the running layer as MFMA fragments (MFMA attention)
   float* norm_ss = nullptr;    // [rows][FIRP_NORM_PIECES] sums of squares left by the last norm
+  float* few_ss = nullptr;     // [FIRP_FEW_ROWS][FIRP_FEW_PIECES] ... by the last projection that did the norm itself
   float2* rope_tab = nullptr;  // [rows][dh/2] (cos, sin) of the running step
   hipStream_t stream = nullptr;
   // weights
@@ -210,6 +211,7 @@ size_t carve(firp_ctx* c, char* base) {
   c->rope_tab = cv.take<float2>((size_t)Rw * d.head_dim / 2);
   c->argmax_scratch = cv.take<char>(argmax_scratch_bytes(Rp, d.b_max));
   c->norm_ss = cv.take<float>((size_t)Rw * FIRP_NORM_PIECES);
+  if (c->dtype == FIRP_BF16) c->few_ss = cv.take<float>((size_t)FIRP_FEW_ROWS * FIRP_FEW_PIECES);
   c->q_frag = cv.take<bf16>(attention_q_frag_elems(Rw, d.max_batch, d.n_q_heads, d.head_dim));
   auto act = [&](Act& a, int ld) {
     a.ld = ld;
@@ -407,6 +409,19 @@ Partial project_stacked(firp_ctx* c, const Act& in, const void* w0, int n0, cons
   return q;
 }
 
+// A projection of a few rows with its consumer as epilogue (see gemm_few.hip).
+void project_few(firp_ctx* c, int epi, const Act& in, const void* w_packed, int rows, int n, int K, const RowScale& rs,
+                 const FewOut& out) {
+  bool timed = c->time_gemm && c->ev_used + 2 <= c->ev.size();
+  if (timed) (void)hipEventRecord(c->ev[c->ev_used++], c->stream);
+  launch_gemm_few(epi, in, rows, w_packed, n, K, rs, out, c->stream);
+  if (timed) {
+    (void)hipEventRecord(c->ev[c->ev_used++], c->stream);
+    c->gemm_bytes += 2.0 * (double)n * (double)K;
+    c->gemm_launches += 1;
+  }
+}
+
 // Every projection shape of the model is one the MFMA kernel takes.
 bool mfma_shapes_ok(const firp_model_desc& d, int qkv_ld) {
   const int qd = d.n_q_heads * d.head_dim;
@@ -465,7 +480,11 @@ firp_status forward(firp_ctx* c, int B, int N, int n_anchor, bool head, int max_
   launch_rope_table(rt, c->st.p0, chain ? seq0 : -1, real_rows + k_act * n_anchor_rows, d.head_dim, d.rope_base, c->rope_tab, s);
   Partial pending{};  // projection output not yet added to the residual stream
   // 1/rms of the latest norm, applied by the kernel that consumes the projection behind it
-  const RowScale rs{c->norm_ss, norm_pieces(d.d_model), 1.0f / (float)d.d_model, d.rms_eps};
+  const RowScale rs_norm{c->norm_ss, norm_pieces(d.d_model), FIRP_NORM_PIECES, 1.0f / (float)d.d_model, d.rms_eps};
+  const RowScale rs_few{c->few_ss, (d.d_model + 15) / 16, FIRP_FEW_PIECES, 1.0f / (float)d.d_model, d.rms_eps};
+  const RowScale rs_one{};   // scaled already
+  RowScale rs = rs_norm;
+  bool normed = false;       // act_d and rs hold the norm of all rows of x already
   int pending_rows = 0;
   int m = 0;  // steps whose pseudo rows are alive
   PseudoBias pbias{};
@@ -495,6 +514,7 @@ firp_status forward(firp_ctx* c, int B, int N, int n_anchor, bool head, int max_
         }
       }
       m = m_new;
+      normed = false;
     }
     const int rows = real_rows + m * n_anchor_rows;
     const int n_local = N + m * n_anchor;
@@ -503,9 +523,20 @@ firp_status forward(firp_ctx* c, int B, int N, int n_anchor, bool head, int max_
         if (pending.p) launch_add_partial(c->x, pending, pending_rows, d.d_model, s);
         break;
       }
-      launch_add_rmsnorm(c->x, pending, rows, d.d_model, c->norm_final, c->dtype, c->act_d, sp, c->norm_ss, s);
-      Partial lg = project(c, c->act_d, c->lm_head, c->packed ? c->pk_head : nullptr, rows, d.vocab, d.d_model,
-                           d.vocab, 0, nullptr);
+      if (!normed) {
+        launch_add_rmsnorm(c->x, pending, rows, d.d_model, c->norm_final, c->dtype, c->act_d, sp, c->norm_ss, s);
+        rs = rs_norm;
+      }
+      Partial lg{c->part, 1, 0, d.vocab};
+      if (normed) {
+        FewOut fo{};
+        fo.y = c->part;
+        fo.ld = d.vocab;
+        project_few(c, FEW_PLAIN, c->act_d, c->pk_head, rows, d.vocab, d.d_model, rs, fo);
+        rs = rs_one;
+      } else {
+        lg = project(c, c->act_d, c->lm_head, c->packed ? c->pk_head : nullptr, rows, d.vocab, d.d_model, d.vocab, 0, nullptr);
+      }
       // the logits themselves are written only on request (tests, the training forward): the step
       // needs the greedy token of every node and the top-b ids of every pseudo row, nothing else
       const bool want_logits = c->keep_logits || c->force_logits;
@@ -519,9 +550,23 @@ firp_status forward(firp_ctx* c, int B, int N, int n_anchor, bool head, int max_
       launch_add_partial(c->x, pending, pending_rows, d.d_model, s);
       pending = Partial{};
     }
-    launch_add_rmsnorm(c->x, pending, rows, d.d_model, c->n1[layer], c->dtype, c->act_d, sp, c->norm_ss, s);
-    Partial q = project_stacked(c, c->act_d, c->wq[layer], qd, c->wk[layer], kvd, c->wv[layer], kvd,
-                                c->packed ? c->pk_qkv[layer] : nullptr, rows, d.d_model);
+    if (!normed) {
+      launch_add_rmsnorm(c->x, pending, rows, d.d_model, c->n1[layer], c->dtype, c->act_d, sp, c->norm_ss, s);
+      rs = rs_norm;
+    }
+    normed = false;
+    const bool few = c->gemm_kind == 1 && sp && c->packed && gemm_few_pays(rows, d.d_model, qd, c->qkv_ld, d.d_ffn);
+    FewOut fo{};
+    Partial q{c->part, 1, 0, c->qkv_ld};
+    if (few) {
+      fo.y = c->part;
+      fo.ld = c->qkv_ld;
+      project_few(c, FEW_PLAIN, c->act_d, c->pk_qkv[layer], rows, c->qkv_ld, d.d_model, rs, fo);
+      rs = rs_one;
+    } else {
+      q = project_stacked(c, c->act_d, c->wq[layer], qd, c->wk[layer], kvd, c->wv[layer], kvd,
+                          c->packed ? c->pk_qkv[layer] : nullptr, rows, d.d_model);
+    }
     KvView kv = kv_view(c, layer);
     if (c->attn_kind == 1 && sp) {
       launch_rope_kv_tiles(q, rs, d.n_q_heads, B, N, n_local - N, n_anchor, seq0, c->st.p0, c->rope_tab, c->q_frag, kv,
@@ -533,6 +578,22 @@ firp_status forward(firp_ctx* c, int B, int N, int n_anchor, bool head, int max_
       launch_rope_kv(q, rs, rows, d.n_q_heads, rt, c->st.p0, c->rope_tab, c->act_q, sp, kv, c->dtype, s);
       launch_attention_simple(c->act_q, sp, rows, d.n_q_heads, rt, c->st.p0, kv, c->dtype, c->act_o, n_local,
                               max_ctx_now + n_local, s);
+    }
+    if (few) {
+      fo.x = c->x;
+      fo.ss = c->few_ss;
+      fo.act = c->act_d;
+      fo.gain = (const bf16*)c->n2[layer];
+      project_few(c, FEW_RESID, c->act_o, c->pk_o[layer], rows, d.d_model, qd, rs_one, fo);
+      fo.act = c->act_f;
+      project_few(c, FEW_SWIGLU, c->act_d, c->pk_gu[layer], rows, 2 * d.d_ffn, d.d_model, rs_few, fo);
+      fo.act = c->act_d;   // with the norm in front of what follows this layer
+      fo.gain = (const bf16*)(layer + 1 < d.n_layers ? c->n1[layer + 1] : c->norm_final);
+      project_few(c, FEW_RESID, c->act_f, c->pk_d[layer], rows, d.d_model, d.d_ffn, rs_one, fo);
+      rs = rs_few;
+      normed = true;
+      pending = Partial{};
+      continue;
     }
     Partial o = project(c, c->act_o, c->wo[layer], c->packed ? c->pk_o[layer] : nullptr, rows, d.d_model, qd,
                         d.d_model, 0, nullptr);

@@ -149,6 +149,21 @@ void launch_pack_weights(const WSeg& src, int n, int K, void* dst, hipStream_t s
 // partials[s][r][c] at out + s*part_stride + r*ld + c for c < n
 void launch_gemm_mfma(const Act& x, const void* w_packed, float* out, int ld, size_t part_stride, int rows,
                       int n, int K, const GemmPlan& plan, hipStream_t s);
+// Projections of up to FIRP_FEW_ROWS rows that finish their outputs themselves; see gemm_few.hip
+#define FIRP_FEW_ROWS 16
+#define FIRP_FEW_PIECES 512   // pieces of a row's sum of squares that FEW_RESID leaves (16 columns each)
+enum { FEW_PLAIN = 0, FEW_SWIGLU = 1, FEW_RESID = 2 };
+struct FewOut {
+  float* y;           // FEW_PLAIN: [rows][ld], scaled
+  int ld;
+  Act act;            // FEW_SWIGLU: [rows][n / 2]; FEW_RESID: [rows][n]
+  float* x;           // FEW_RESID: residual stream [rows][n]
+  const bf16* gain;
+  float* ss;          // [rows][FIRP_FEW_PIECES]
+};
+bool gemm_few_pays(int rows, int d_model, int q_dim, int qkv_dim, int d_ffn);
+void launch_gemm_few(int epi, const Act& x, int rows, const void* w_packed, int n, int K, const RowScale& rs,
+                     const FewOut& out, hipStream_t s);
 void launch_split_act(const float* x, int rows, int ld, const Act& out, hipStream_t s);
 void launch_reduce_partials(const Partial& p, float* y, int rows, hipStream_t s);
 void launch_stream_read(const void* src, size_t bytes, unsigned* sink, hipStream_t s);
