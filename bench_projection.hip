@@ -79,14 +79,15 @@ int main(int argc, char** argv) {
     CK(hipFree(pool));
     int rp = (rows + 15) / 16 * 16;
     unsigned short* xp;
-    CK(hipMalloc(&xp, (size_t)rp * act_row(sh.K) * 2));
-    hipLaunchKernelGGL(k_fill_bf16, dim3(512), dim3(256), 0, 0, xp, (size_t)rp * act_row(sh.K), 3u);
+    CK(hipMalloc(&xp, (size_t)rp * act_row_spread(sh.K) * 2));
+    hipLaunchKernelGGL(k_fill_bf16, dim3(512), dim3(256), 0, 0, xp, (size_t)rp * act_row_spread(sh.K), 3u);
     GemmPlan plan = force_nw ? gemm_mfma_plan_ex(rows, sh.n, sh.K, force_s, force_nw) : gemm_mfma_plan(rows, sh.n, sh.K, force_s);
     float* part;
     CK(hipMalloc(&part, (size_t)plan.S * rp * sh.n * 4));
     Act a{};
     a.pl = (bf16*)xp;
     a.ld = sh.K;
+    a.row = act_row_spread(sh.K);
     auto run = [&](int i) {
       launch_gemm_mfma(a, packed + (size_t)(i % cnt) * pbytes, part, sh.n, (size_t)rp * sh.n, rows, sh.n, sh.K, plan, 0);
     };

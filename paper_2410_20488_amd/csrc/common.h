@@ -48,15 +48,19 @@ __device__ __forceinline__ void store_elt<bf16>(bf16* p, float v) { *p = f32_to_
 // a time without fetching half lines.
 struct Act {
   float* f32;  // [rows][ld] or nullptr
-  bf16* pl;    // [rows][act_row(ld)] or nullptr
+  bf16* pl;    // [rows][row] or nullptr
   int ld;      // columns
+  int row;     // bf16 elements between rows of planes, at least act_row(ld)
 };
 // bf16 elements of a row of planes (a last group of fewer than 32 columns is padded; nobody writes the
 // padding, and readers must not use it)
-__host__ __device__ __forceinline__ int act_row(int ld) { return (ld + 31) / 32 * 64; }
+inline int act_row(int ld) { return (ld + 31) / 32 * 64; }
+// ... and between the rows of a buffer: an odd multiple of 256 bytes (or of 128), so that the lines which
+// a projection stages at one time, the same columns of every row, spread over all channels of an L2
+inline int act_row_spread(int ld) { return act_row(ld) + (act_row(ld) % 256 == 0 ? 128 : 0); }
 // element of column `col` in the hi plane; the lo plane's is 32 further
 __device__ __forceinline__ bf16* act_at(const Act& a, int row, int col) {
-  return a.pl + (size_t)row * act_row(a.ld) + (col >> 5) * 64 + (col & 31);
+  return a.pl + (size_t)row * a.row + (col >> 5) * 64 + (col & 31);
 }
 
 template <bool SPLIT>

@@ -216,7 +216,8 @@ size_t carve(firp_ctx* c, char* base) {
   auto act = [&](Act& a, int ld) {
     a.ld = ld;
     a.f32 = cv.take<float>((size_t)Rp * ld);
-    a.pl = cv.take<bf16>((size_t)Rw * act_row(ld));
+    a.row = act_row_spread(ld);
+    a.pl = cv.take<bf16>((size_t)Rw * a.row);
   };
   act(c->act_d, d.d_model);
   act(c->act_q, qd);
@@ -1397,8 +1398,9 @@ static void gemm_in_workspace(const float* x, const void* w, float* y, int rows,
   size_t rp = align_up(rows, 16);
   Act a{};
   a.ld = k_dim;
+  a.row = act_row(k_dim);
   a.pl = (bf16*)workspace;
-  float* part = (float*)((char*)workspace + align_up(rp * act_row(k_dim) * 2, 256));
+  float* part = (float*)((char*)workspace + align_up(rp * a.row * 2, 256));
   char* end = (char*)workspace + firp_gemm_workspace_bytes(rows, n, k_dim) - 512;
   void* wpk = end - align_up(gemm_packed_bytes(n, k_dim), 256);
   launch_split_act(x, rows, k_dim, a, s);

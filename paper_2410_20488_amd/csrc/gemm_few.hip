@@ -216,7 +216,7 @@ void launch_gemm_few(int epi, const Act& x, int rows, const void* w_packed, int 
                      const FewOut& out, hipStream_t s) {
   const int outs = epi == FEW_SWIGLU ? n / 32 : (n + 15) / 16, per = few_tiles(epi, n);
   auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3((outs + per - 1) / per), dim3(64 * FEW_WAVES), 0, s, x.pl, act_row(x.ld), rows,
+    hipLaunchKernelGGL(kern, dim3((outs + per - 1) / per), dim3(64 * FEW_WAVES), 0, s, x.pl, x.row, rows,
                        (const char*)w_packed, n, K, rs, out);
   };
   const bool tail = K % 64 != 0;

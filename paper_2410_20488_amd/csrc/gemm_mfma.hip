@@ -166,7 +166,7 @@ void launch_pack_weights(const WSeg& src, int n, int K, void* dst, hipStream_t s
 void launch_gemm_mfma(const Act& x, const void* w_packed, float* out, int ld, size_t part_stride, int rows, int n,
                       int K, const GemmPlan& plan, hipStream_t s) {
   const char* w = (const char*)w_packed;
-  const int ldx = act_row(x.ld);
+  const int ldx = x.row;
   if (plan.xt) {
     launch_gemm_tall(x.pl, ldx, rows, w, n, K, out, ld, part_stride, plan, s);
     return;

@@ -33,21 +33,49 @@ void launch_fill_tokens(const SeqState& st, const TreeTab& tt, int B, const int*
 }
 
 // ------------------------------------------------------------------------------------------
+// four consecutive elements; a caller's matrix need only be aligned to its elements
+__device__ __forceinline__ void load4(const float* p, float (&v)[4]) {
+  if (((size_t)p & 15) == 0) {
+    const float4 q = *(const float4*)p;
+    v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = p[i];
+  }
+}
+__device__ __forceinline__ void load4(const bf16* p, float (&v)[4]) {
+  if (((size_t)p & 7) == 0) {
+    const uint2 q = *(const uint2*)p;
+    v[0] = __uint_as_float(q.x << 16);
+    v[1] = __uint_as_float(q.x & 0xffff0000u);
+    v[2] = __uint_as_float(q.y << 16);
+    v[3] = __uint_as_float(q.y & 0xffff0000u);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = to_f32(p[i]);
+  }
+}
+
 template <typename WT>
 __global__ void k_embed(const WT* __restrict__ E, const int* __restrict__ tok, int d, int vocab, float* x) {
   int r = blockIdx.x;
   int t = tok[r];
   if (t < 0 || t >= vocab) t = 0;  // "no candidate" (-1), or an id derived from non-finite logits
   const WT* e = E + (size_t)t * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) x[(size_t)r * d + i] = to_f32(e[i]);
+  const int i = (blockIdx.y * blockDim.x + threadIdx.x) * 4;   // d % 4 == 0
+  if (i < d) {
+    float v[4];
+    load4(e + i, v);
+    *(float4*)(x + (size_t)r * d + i) = make_float4(v[0], v[1], v[2], v[3]);
+  }
 }
 
 void launch_embed(const void* embed, int dtype, const int* tok, int rows, int d, int vocab, float* x,
                   hipStream_t s) {
   if (dtype == DT_BF16)
-    hipLaunchKernelGGL(k_embed<bf16>, dim3(rows), dim3(256), 0, s, (const bf16*)embed, tok, d, vocab, x);
+    hipLaunchKernelGGL(k_embed<bf16>, dim3(rows, (d + 1023) / 1024), dim3(256), 0, s, (const bf16*)embed, tok, d, vocab, x);
   else
-    hipLaunchKernelGGL(k_embed<float>, dim3(rows), dim3(256), 0, s, (const float*)embed, tok, d, vocab, x);
+    hipLaunchKernelGGL(k_embed<float>, dim3(rows, (d + 1023) / 1024), dim3(256), 0, s, (const float*)embed, tok, d, vocab, x);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -65,6 +93,8 @@ __global__ __launch_bounds__(256) void k_add_rmsnorm(float* x, Partial part, int
   if (i < (d >> 2)) {
     float4* xr = (float4*)(x + (size_t)r * d);
     float4 a = xr[i];
+    float g[4];
+    if constexpr (NORM) load4(gain + i * 4, g);
     if (part.p) {
       const float* pp = part.p + (size_t)r * part.ld + (size_t)i * 4;
       float4 q[SMAX];
@@ -83,8 +113,7 @@ __global__ __launch_bounds__(256) void k_add_rmsnorm(float* x, Partial part, int
     }
     if constexpr (NORM) {
       ss = a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w;
-      act_store4<SPLIT>(out, r, i * 4, a.x * to_f32(gain[i * 4 + 0]),
-                        a.y * to_f32(gain[i * 4 + 1]), a.z * to_f32(gain[i * 4 + 2]), a.w * to_f32(gain[i * 4 + 3]));
+      act_store4<SPLIT>(out, r, i * 4, a.x * g[0], a.y * g[1], a.z * g[2], a.w * g[3]);
     }
   }
   if constexpr (NORM) {
@@ -239,17 +268,18 @@ void launch_swiglu(const Partial& gate_up, const RowScale& rs, int rows, int d_f
 // stream.  gather: rows of x -> projection input; scatter: projection output (+bias) -> x.
 template <bool SPLIT>
 __global__ void k_gather_rows(const float* __restrict__ x, const int* __restrict__ src, int d, Act out) {
-  int g = blockIdx.x;
-  const float* xr = x + (size_t)src[g] * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) act_store<SPLIT>(out, g, i, xr[i]);
+  const int g = blockIdx.x, i = (blockIdx.y * blockDim.x + threadIdx.x) * 4;   // d % 4 == 0
+  if (i >= d) return;
+  const float4 v = *(const float4*)(x + (size_t)src[g] * d + i);
+  act_store4<SPLIT>(out, g, i, v.x, v.y, v.z, v.w);
 }
 
 void launch_gather_rows(const float* x, const int* src_rows, int rows, int d, const Act& out,
                         bool split, hipStream_t s) {
   if (split)
-    hipLaunchKernelGGL(k_gather_rows<true>, dim3(rows), dim3(256), 0, s, x, src_rows, d, out);
+    hipLaunchKernelGGL(k_gather_rows<true>, dim3(rows, (d + 1023) / 1024), dim3(256), 0, s, x, src_rows, d, out);
   else
-    hipLaunchKernelGGL(k_gather_rows<false>, dim3(rows), dim3(256), 0, s, x, src_rows, d, out);
+    hipLaunchKernelGGL(k_gather_rows<false>, dim3(rows, (d + 1023) / 1024), dim3(256), 0, s, x, src_rows, d, out);
 }
 
 // y holds the k maps' outputs side by side (map i in columns [i*d, (i+1)*d)), or one map's output
@@ -289,29 +319,28 @@ __device__ __forceinline__ bool better(float v, int id, const Best& o) {
 }
 
 // Two levels.  k_argmax_part: blockIdx = (row, vocabulary segment); one pass over the segment,
-// every thread keeps the best BM entries of its strided share in registers (sorted insertion),
-// then `want` rounds of a block-wide arg-best over the threads' current heads leave the
+// every thread keeps the best BM entries of its share in registers (sorted insertion), then `want`
+// rounds of a block-wide arg-best over the threads' current heads leave the
 // segment's best entries, in order, in cand[row][segment][BM].  k_argmax_merge: one block per
 // row picks the row's top entries out of the segments' candidates the same way.
 #define FIRP_ARGMAX_SEGS 8
-template <int BM>
+// VEC: rows of 16-byte aligned float4 (ld and vocab multiples of 4); four tokens at a time, the loads of
+// two such groups and all their splits in flight together (one token after the other, with a round
+// trip per split, the kernel took 25 us for 67 rows of 32000 tokens and 15 us for one, now 20 and 10).
+template <int BM, bool VEC>
 __global__ __launch_bounds__(256) void k_argmax_part(Partial lg, RowScale rs, float* logits_out, int real_rows,
                                                      int vocab, int b_max, Best* __restrict__ cand) {
-  __shared__ float sv[256];
-  __shared__ int si[256];
+  __shared__ Best best_of[2][4];
   const int r = blockIdx.x, seg = blockIdx.y, tid = threadIdx.x;
   const size_t off = (size_t)r * lg.ld;
   const bool copy = logits_out && (lg.S > 1 || logits_out != lg.p || rs.ss);
   const int want = (r < real_rows) ? 1 : b_max;
-  const float scale = row_scale(rs, r);
   const int seg_len = ((vocab + FIRP_ARGMAX_SEGS - 1) / FIRP_ARGMAX_SEGS + 3) & ~3;
   const int t0 = seg * seg_len, t1 = min(vocab, t0 + seg_len);
   Best mine[BM];
 #pragma unroll
   for (int e = 0; e < BM; ++e) mine[e] = Best{-__builtin_inff(), 0x7fffffff};
-  for (int t = t0 + tid; t < t1; t += 256) {
-    float v = partial_sum(lg, off + t) * scale;
-    if (copy) logits_out[(size_t)r * vocab + t] = v;
+  auto take = [&](float v, int t) {
     if (better(v, t, mine[BM - 1])) {
       mine[BM - 1] = Best{v, t};
 #pragma unroll
@@ -322,25 +351,70 @@ __global__ __launch_bounds__(256) void k_argmax_part(Partial lg, RowScale rs, fl
           mine[e] = tmp;
         }
     }
+  };
+  if constexpr (VEC) {
+    constexpr int G = 2, SB = 4;   // groups of four tokens, splits per batch of loads
+    const float scale = row_scale(rs, r);
+    for (int t = t0 + tid * 4; t < t1; t += G * 1024) {
+      float4 v[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) v[g] = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int s0 = 0; s0 < lg.S; s0 += SB) {
+        float4 q[G][SB];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+          for (int e = 0; e < SB; ++e)
+            if (s0 + e < lg.S && t + g * 1024 < t1)
+              q[g][e] = *(const float4*)(lg.p + off + t + g * 1024 + (size_t)(s0 + e) * lg.stride);
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+          for (int e = 0; e < SB; ++e)
+            if (s0 + e < lg.S && t + g * 1024 < t1) {
+              if (s0 + e == 0) {
+                v[g] = q[g][e];
+              } else {
+                v[g].x += q[g][e].x; v[g].y += q[g][e].y; v[g].z += q[g][e].z; v[g].w += q[g][e].w;
+              }
+            }
+      }
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const int tg = t + g * 1024;
+        if (tg >= t1) continue;
+        v[g].x *= scale; v[g].y *= scale; v[g].z *= scale; v[g].w *= scale;
+        if (copy) *(float4*)(logits_out + (size_t)r * vocab + tg) = v[g];
+        take(v[g].x, tg);
+        take(v[g].y, tg + 1);
+        take(v[g].z, tg + 2);
+        take(v[g].w, tg + 3);
+      }
+    }
+  } else {
+    const float scale = row_scale(rs, r);
+    for (int t = t0 + tid; t < t1; t += 256) {
+      const float v = partial_sum(lg, off + t) * scale;
+      if (copy) logits_out[(size_t)r * vocab + t] = v;
+      take(v, t);
+    }
   }
   Best* out = cand + ((size_t)r * FIRP_ARGMAX_SEGS + seg) * BM;
   for (int p = 0; p < want; ++p) {
-    sv[tid] = mine[0].v;
-    si[tid] = mine[0].id;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if (tid < w) {
-        Best o{sv[tid + w], si[tid + w]};
-        Best m{sv[tid], si[tid]};
-        if (better(o.v, o.id, m)) {
-          sv[tid] = o.v;
-          si[tid] = o.id;
-        }
-      }
-      __syncthreads();
+    Best m = mine[0];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const Best other{__shfl_xor(m.v, o, 64), __shfl_xor(m.id, o, 64)};
+      if (better(other.v, other.id, m)) m = other;
     }
-    const Best win{sv[0], si[0]};
-    __syncthreads();
+    if ((tid & 63) == 0) best_of[p & 1][tid >> 6] = m;
+    __syncthreads();   // (the other half of best_of is written next: one barrier per round is enough)
+    Best win = best_of[p & 1][0];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) {
+      const Best other = best_of[p & 1][w];
+      if (better(other.v, other.id, win)) win = other;
+    }
     if (mine[0].id == win.id && win.id != 0x7fffffff) {  // the owner pops its head
 #pragma unroll
       for (int e = 0; e + 1 < BM; ++e) mine[e] = mine[e + 1];
@@ -396,11 +470,15 @@ void launch_argmax_topb(const Partial& logits, const RowScale& rs, float* logits
                         int vocab, int b_max, int* amax, int* top, void* scratch, hipStream_t s) {
   Best* cand = (Best*)scratch;
   dim3 g(rows, FIRP_ARGMAX_SEGS);
+  auto part = [&](auto kern) {
+    hipLaunchKernelGGL(kern, g, dim3(256), 0, s, logits, rs, logits_out, real_rows, vocab, b_max, cand);
+  };
+  const bool vec = logits.ld % 4 == 0 && vocab % 4 == 0;   // (buffers are 256-byte aligned, so is a split's stride then)
   if (b_max <= 8) {
-    hipLaunchKernelGGL(k_argmax_part<8>, g, dim3(256), 0, s, logits, rs, logits_out, real_rows, vocab, b_max, cand);
+    if (vec) part(k_argmax_part<8, true>); else part(k_argmax_part<8, false>);
     hipLaunchKernelGGL(k_argmax_merge<8>, dim3(rows), dim3(64), 0, s, cand, real_rows, vocab, b_max, amax, top);
   } else {
-    hipLaunchKernelGGL(k_argmax_part<16>, g, dim3(256), 0, s, logits, rs, logits_out, real_rows, vocab, b_max, cand);
+    if (vec) part(k_argmax_part<16, true>); else part(k_argmax_part<16, false>);
     hipLaunchKernelGGL(k_argmax_merge<16>, dim3(rows), dim3(64), 0, s, cand, real_rows, vocab, b_max, amax, top);
   }
 }
