@@ -124,6 +124,16 @@ struct RowScale {
   float inv_d, eps;
 };
 #define FIRP_NORM_PIECES 8
+// the same where the pieces are the norm kernel's: all of them in two loads
+__device__ __forceinline__ float row_scale8(const RowScale& rs, int r) {
+  const float4* q = (const float4*)(rs.ss + (size_t)r * FIRP_NORM_PIECES);
+  const float4 a = q[0], b = q[1];
+  const float v[FIRP_NORM_PIECES] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+  float t = 0.f;
+#pragma unroll
+  for (int i = 0; i < FIRP_NORM_PIECES; ++i) t += i < rs.pieces ? v[i] : 0.f;
+  return 1.0f / sqrtf(t * rs.inv_d + rs.eps);
+}
 __device__ __forceinline__ float row_scale(const RowScale& rs, int r) {
   if (!rs.ss) return 1.0f;
   float t = 0.f;

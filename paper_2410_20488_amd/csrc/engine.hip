@@ -410,17 +410,25 @@ Partial project_stacked(firp_ctx* c, const Act& in, const void* w0, int n0, cons
   return q;
 }
 
-// A projection of a few rows with its consumer as epilogue (see gemm_few.hip).
-void project_few(firp_ctx* c, int epi, const Act& in, const void* w_packed, int rows, int n, int K, const RowScale& rs,
-                 const FewOut& out) {
+// Projections that are one launch with their consumer as epilogue: of a few rows (see gemm_few.hip), and
+// gate|up of many (gemm_tall.hip).
+template <typename L>
+void timed_projection(firp_ctx* c, int n, int K, L&& launch) {
   bool timed = c->time_gemm && c->ev_used + 2 <= c->ev.size();
   if (timed) (void)hipEventRecord(c->ev[c->ev_used++], c->stream);
-  launch_gemm_few(epi, in, rows, w_packed, n, K, rs, out, c->stream);
+  launch();
   if (timed) {
     (void)hipEventRecord(c->ev[c->ev_used++], c->stream);
     c->gemm_bytes += 2.0 * (double)n * (double)K;
     c->gemm_launches += 1;
   }
+}
+void project_few(firp_ctx* c, int epi, const Act& in, const void* w_packed, int rows, int n, int K, const RowScale& rs,
+                 const FewOut& out) {
+  timed_projection(c, n, K, [&] { launch_gemm_few(epi, in, rows, w_packed, n, K, rs, out, c->stream); });
+}
+void project_swiglu(firp_ctx* c, const Act& in, const void* w_packed, int rows, int F, int K, const RowScale& rs, const Act& out) {
+  timed_projection(c, 2 * F, K, [&] { launch_gemm_swiglu(in, w_packed, rows, F, K, rs, out, c->stream); });
 }
 
 // Every projection shape of the model is one the MFMA kernel takes.
@@ -599,9 +607,14 @@ firp_status forward(firp_ctx* c, int B, int N, int n_anchor, bool head, int max_
     Partial o = project(c, c->act_o, c->wo[layer], c->packed ? c->pk_o[layer] : nullptr, rows, d.d_model, qd,
                         d.d_model, 0, nullptr);
     launch_add_rmsnorm(c->x, o, rows, d.d_model, c->n2[layer], c->dtype, c->act_d, sp, c->norm_ss, s);
-    Partial g = project_stacked(c, c->act_d, c->wg[layer], d.d_ffn, c->wu[layer], d.d_ffn, nullptr, 0,
-                                c->packed ? c->pk_gu[layer] : nullptr, rows, d.d_model);
-    launch_swiglu(g, rs, rows, d.d_ffn, c->act_f, sp, s);
+    rs = rs_norm;
+    if (c->gemm_kind == 1 && sp && c->packed && gemm_swiglu_fused(rows, d.d_ffn, d.d_model)) {
+      project_swiglu(c, c->act_d, c->pk_gu[layer], rows, d.d_ffn, d.d_model, rs, c->act_f);
+    } else {
+      Partial g = project_stacked(c, c->act_d, c->wg[layer], d.d_ffn, c->wu[layer], d.d_ffn, nullptr, 0,
+                                  c->packed ? c->pk_gu[layer] : nullptr, rows, d.d_model);
+      launch_swiglu(g, rs, rows, d.d_ffn, c->act_f, sp, s);
+    }
     pending = project(c, c->act_f, c->wd[layer], c->packed ? c->pk_d[layer] : nullptr, rows, d.d_model, d.d_ffn,
                       d.d_model, 0, nullptr);
     pending_rows = rows;

@@ -6,6 +6,8 @@ namespace firp {
 // the kernel for more than 128 rows (gemm_tall.hip); takes K % 64 == 0 only
 void launch_gemm_tall(const bf16* x, int ldx, int rows, const void* w_packed, int n, int K, float* out, int ld,
                       size_t part_stride, const GemmPlan& plan, hipStream_t s);
+void launch_gemm_tall_swiglu(const bf16* x, int ldx, int rows, const void* w_packed, int F, int K, const RowScale& rs,
+                             const Act& act, const GemmPlan& p, hipStream_t s);
 static bool tall_shape(int rows, int K) { return rows > 128 && K % 64 == 0; }
 
 bool gemm_mfma_supported(int rows, int n, int K) {
@@ -161,6 +163,16 @@ void launch_pack_weights(const WSeg& src, int n, int K, void* dst, hipStream_t s
   const size_t pieces = gemm_packed_bytes(n, K) / 16;
   const unsigned blocks = (unsigned)((pieces + 255) / 256);
   hipLaunchKernelGGL(k_pack_weights, dim3(blocks), dim3(256), 0, s, src, n, K, kp32, pieces, (uint4*)dst);
+}
+
+bool gemm_swiglu_fused(int rows, int F, int K) {
+  if (!tall_shape(rows, K) || F % 16) return false;
+  return gemm_mfma_plan(rows, 2 * F, K, 0).S == 1;
+}
+
+void launch_gemm_swiglu(const Act& x, const void* w_packed, int rows, int F, int K, const RowScale& rs, const Act& act,
+                        hipStream_t s) {
+  launch_gemm_tall_swiglu(x.pl, x.row, rows, w_packed, F, K, rs, act, gemm_mfma_plan(rows, 2 * F, K, 0), s);
 }
 
 void launch_gemm_mfma(const Act& x, const void* w_packed, float* out, int ld, size_t part_stride, int rows, int n,

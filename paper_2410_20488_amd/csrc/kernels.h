@@ -164,6 +164,11 @@ struct FewOut {
 bool gemm_few_pays(int rows, int d_model, int q_dim, int qkv_dim, int d_ffn);
 void launch_gemm_few(int epi, const Act& x, int rows, const void* w_packed, int n, int K, const RowScale& rs,
                      const FewOut& out, hipStream_t s);
+// gate|up of more than 128 rows with SwiGLU as its epilogue, where the projection is not split: act =
+// silu(gate) * up (rs: the row scale of the norm kernel's sums, on both)
+bool gemm_swiglu_fused(int rows, int F, int K);
+void launch_gemm_swiglu(const Act& x, const void* w_packed, int rows, int F, int K, const RowScale& rs, const Act& act,
+                        hipStream_t s);
 void launch_split_act(const float* x, int rows, int ld, const Act& out, hipStream_t s);
 void launch_reduce_partials(const Partial& p, float* y, int rows, hipStream_t s);
 void launch_stream_read(const void* src, size_t bytes, unsigned* sink, hipStream_t s);
