@@ -55,6 +55,8 @@ void launch_embed(const void* embed, int dtype, const int* tok, int rows, int d,
 int norm_pieces(int d);
 void launch_add_rmsnorm(float* x, const Partial& part, int rows, int d, const void* gain, int dtype, const Act& out,
                         bool split, float* ss_out, hipStream_t s);
+// dst[g] = x[row0 + g] + sum of partials of that row (if part.p), g < rows
+void launch_copy_rows(const float* x, const Partial& part, int row0, int rows, int d, float* dst, hipStream_t s);
 // Only the residual update, no norm output (used before the projection at the FIRP layer).
 void launch_add_partial(float* x, const Partial& part, int rows, int d, hipStream_t s);
 // qkv partials -> rotary q (activation planes, [rows][Hq*dh]) and K / V^T into the cache.

@@ -148,6 +148,25 @@ void launch_add_partial(float* x, const Partial& part, int rows, int d, hipStrea
                      (const float*)nullptr, none, (float*)nullptr);
 }
 
+__global__ __launch_bounds__(256) void k_copy_rows(const float* __restrict__ x, Partial part, int row0, int d,
+                                                   float* __restrict__ dst) {
+  const int g = blockIdx.x, i = (blockIdx.y * 256 + threadIdx.x) * 4;   // d % 4 == 0
+  if (i >= d) return;
+  float4 a = *(const float4*)(x + (size_t)(row0 + g) * d + i);
+  for (int sp = 0; part.p && sp < part.S; ++sp) {
+    const float4 q = *(const float4*)(part.p + (size_t)sp * part.stride + (size_t)(row0 + g) * part.ld + i);
+    a.x += q.x;
+    a.y += q.y;
+    a.z += q.z;
+    a.w += q.w;
+  }
+  *(float4*)(dst + (size_t)g * d + i) = a;
+}
+
+void launch_copy_rows(const float* x, const Partial& part, int row0, int rows, int d, float* dst, hipStream_t s) {
+  hipLaunchKernelGGL(k_copy_rows, dim3(rows, (d + 1023) / 1024), dim3(256), 0, s, x, part, row0, d, dst);
+}
+
 // ------------------------------------------------------------------------------------------
 // Rotary embedding (half-split pairs (j, j+dh/2), angle pos * base^(-2j/dh)) on q and k at the
 // row's position id p0 + pos_off (tree nodes keep their original positions; siblings share
