@@ -305,12 +305,12 @@ void setup_geometry(firp_ctx* c, const firp_model_desc* d, int k) {
   size_t widest_layer = std::max<size_t>({(size_t)2 * d->d_ffn, (size_t)c->qkv_ld, (size_t)d->d_model});
   size_t widest = std::max<size_t>((size_t)d->vocab, widest_layer);
   c->part_elems = (size_t)c->Rpad * (widest + FIRP_PART_PAD) * 8;
-  // prompt chunks of bf16 models: FIRP_CHUNK_ROWS rows at a time (see firp_prefill), which fill the
-  // chip without splitting K much
+  // prompt chunks of bf16 models: FIRP_CHUNK_ROWS rows at a time (see firp_prefill); the partial sums of the
+  // splits that gemm_mfma_plan takes for them at the LLaMA shapes
   c->Rwork = c->Rpad;
   if (d->dtype == FIRP_BF16) {
     c->Rwork = std::max(c->Rpad, std::min(FIRP_CHUNK_ROWS, (int)align_up(d->max_ctx, 16)));
-    c->part_elems = std::max(c->part_elems, (size_t)c->Rwork * (widest_layer + FIRP_PART_PAD) * 2);
+    c->part_elems = std::max(c->part_elems, (size_t)c->Rwork * (widest_layer + FIRP_PART_PAD) * 3);
   }
 }
 
