@@ -54,7 +54,7 @@ GemmPlan gemm_mfma_plan_ex(int rows, int n, int K, int S, int nw) {
 // More than 320 rows fill the chip without splitting K, but one fp32 accumulator over all of K rounds more
 // often than the sums of a split: K is cut at least as often as for 128 rows (`min_split`).  Without
 // that the rms logit error of the 13B shape behind a prompt of 1024 tokens went from 2.01e-3 to 2.32e-3 of a
-// standard deviation.
+// standard deviation.  It costs that prompt 45.2 -> 55.2 ms, one of 8192 tokens at the 7B shape 212 -> 255.
 static GemmPlan tall_plan(int rows, int n, int K, int force_split, int min_split) {
   const int stages = K / KC;
   struct Tile { int nw, xt; double us; };

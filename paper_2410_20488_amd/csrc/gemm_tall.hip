@@ -29,7 +29,7 @@
 //    in LDS a fragment keeps its 1 KiB lane order, so the reads are linear.
 //
 // Measured per launch at the 13B shapes (q|k|v, o, gate|up, down), sustained: 1024 rows 240, 94, 427, 207 us (the
-// best plan; 1.34 PFLOP/s with both planes counted), 256 rows 85, 35, 129, 72 us.  The kernel before it (one
+// fastest split, which the plan takes only where it is no coarser than for 128 rows; 1.34 PFLOP/s with both planes counted), 256 rows 85, 35, 129, 72 us.  The kernel before it (one
 // launch per 256 rows, two barriers per 64 columns, fragments read from LDS behind the barrier they
 // waited for): 328, 157, 538, 310 us and 92, 41, 140, 79 us.
 #include <algorithm>
@@ -320,8 +320,8 @@ void launch_gemm_tall(const bf16* x, int ldx, int rows, const void* w_packed, in
 }
 
 // act = silu(gate) * up of gate|up [2 F][K] (F % 16 == 0) for a plan of one split: the 8 F rows bytes of partial sums
-// are neither written nor read, and there is no kernel to read them.  1023 rows of the 13B shape: 416 us
-// and 26 for the separate kernel -> 411 us; of the 7B shape: 277 and 21 -> 269.
+// are neither written nor read, and there is no kernel to read them.  1023 rows of the 13B shape with K whole:
+// 416 us and 26 for the separate kernel -> 411 us; of the 7B shape: 277 and 21 -> 269.
 void launch_gemm_tall_swiglu(const bf16* x, int ldx, int rows, const void* w_packed, int F, int K, const RowScale& rs,
                              const Act& act, const GemmPlan& p, hipStream_t s) {
   const int blocks = (rows + 64 * p.xt - 1) / (64 * p.xt), tiles = (F + 16 * p.nw - 1) / (16 * p.nw);
